@@ -52,7 +52,8 @@ typedef enum {
 } askit_status;
 
 typedef enum {
-    ASKIT_PREC_FP32 = 0,   /* distances on MFMA in FP32, kernel and sums in FP32 */
+    ASKIT_PREC_FP32 = 0,   /* distances on MFMA with FP32 precision (up to 64 dimensions from
+                              16-bit parts of the FP32 coordinates), kernel and sums in FP32 */
     ASKIT_PREC_BF16X3 = 1  /* distance products as bf16 hi/lo split (hi*hi + hi*lo + lo*hi)
                               on MFMA with FP32 accumulation */
 } askit_precision;
@@ -248,7 +249,7 @@ typedef struct {
     double t_knn_filter_ms;              /* last setup: the kNN filter sweep launches alone (sum) */
     int64_t knn_filter_launches;         /* ... and their number */
     int64_t eval_pairs;                  /* (target, source node) pairs of one evaluation */
-    int64_t eval_chunks;                 /* evaluation work items (up to 64 targets of one source node) */
+    int64_t eval_chunks;                 /* evaluation work items (targets of one source node) */
     int64_t knn_retry_rows;              /* rows whose filter output overflowed (filtered again at
                                             sampled thresholds, then list sweeps if that overflows) */
     int64_t near_lists;                  /* sum over points of |near(i)|: near leaves per point (Alg. 4) */
@@ -416,7 +417,7 @@ typedef struct askit_batch askit_batch;
 
 typedef struct {
     int32_t count, nrhs;
-    int64_t total_points, total_chunks;   /* chunks: evaluation work items of up to 64 targets */
+    int64_t total_points, total_chunks;   /* chunks: evaluation work items */
     int64_t near_entries, far_entries, near_pairs, far_pairs;
     double t_setup_ms;
     double t_skel_ms;           /* of which the fused skeletonization of all instances (the

@@ -118,14 +118,21 @@ void gather_f64(const double *src, const int32_t *idx, int64_t n, double *dst, h
 }
 
 // Bandwidth per source: fixed h, or the distance to the b-th neighbour.
-__global__ void k_bandwidth(const double *__restrict__ knn_d, int64_t N, int kappa, int b, double h,
-                            double *__restrict__ hs, int32_t *bad)
+// bad[0]: set for one that is not positive; bad[1]: the smallest (FP32 bits).
+__global__ __launch_bounds__(256) void k_bandwidth(const double *__restrict__ knn_d, int64_t N, int kappa, int b,
+                                                   double h, double *__restrict__ hs, int32_t *bad)
 {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    double v = b > 0 ? sqrt(knn_d[j * kappa + (b - 1)]) : h;
-    if (!(v > 0.0)) atomicOr(bad, 1);
-    hs[j] = v;
+    int lo = 0x7f7fffff;
+    if (j < N) {
+        double v = b > 0 ? sqrt(knn_d[j * kappa + (b - 1)]) : h;
+        if (!(v > 0.0)) atomicOr(bad, 1);
+        else lo = __float_as_int((float)v);
+        hs[j] = v;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) lo = min(lo, __shfl_xor(lo, o));
+    if ((threadIdx.x & 63) == 0) atomicMin(&bad[1], lo);
 }
 
 // g = -log2(e) / (2 h^2) per tree position (FP32 exponent factor of exp2).
@@ -333,7 +340,7 @@ void query_points(askit_handle *h, const WeightSet &ws, const float *Y, int64_t 
     build_query_interactions(h, nbs, M, qslabs, ptr, node, mask, nen, nef, tmp, s, nseg > 1 ? segs : nullptr,
                              nqslab);
     PairLists L;
-    build_pairs(h, qslabs, nqslab, M, ptr, node, mask, nen, nef, L, ta, s, nseg);
+    build_pairs(h, qslabs, nqslab, M, ptr, node, mask, nen, nef, L, ta, s, false, nseg);
     float *part = (float *)ta(sizeof(float) * std::max<int64_t>(L.npairs, 1) * ws.R);
     evaluate(h, ws, Ys, L, order, U, ldu, part, s);
     HIPC(hipStreamSynchronize(s));
@@ -667,12 +674,17 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
         HIPC(ws_free(bad, s));
     }
     HIPC(hipMemsetAsync(flag, 0, sizeof(int32_t), s));
+    HIPC(hipMemsetAsync(flag + 1, 0x7f, sizeof(int32_t), s));
     hipLaunchKernelGGL(k_bandwidth, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, h->knn_d, N,
                        kappa, p->bw_neighbor, p->bandwidth, h->hsrc, flag);
     HIPC(hipGetLastError());
-    HIPC(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    int32_t hbw[2] = {0, 0};
+    HIPC(hipMemcpyAsync(hbw, flag, sizeof(hbw), hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
-    if (hflag) fail(ASKIT_ERR_INVALID_ARG, "zero bandwidth (duplicate points with variable bandwidth)");
+    if (hbw[0]) fail(ASKIT_ERR_INVALID_ARG, "zero bandwidth (duplicate points with variable bandwidth)");
+    float hmin;
+    std::memcpy(&hmin, &hbw[1], sizeof(hmin));
+    h->ev_sc = eval_scale(h->varh ? (double)hmin : p->bandwidth, h->varh, mx);
     hipLaunchKernelGGL(k_gfactor, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, h->hsrc, h->perm,
                        N, h->gt);
     HIPC(hipGetLastError());
@@ -705,7 +717,7 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
         HIPC(hipEventRecord(ei[0], s));
         build_interactions(hp, s);
         build_pairs(hp, hp->d_slabs, (int64_t)hp->slabs.size(), N, hp->sl_ptr, hp->sl_node, hp->sl_mask,
-                    hp->near_entries, hp->far_entries, hp->pairs, [hp](size_t b) { return hp->alloc(b, false); }, s);
+                    hp->near_entries, hp->far_entries, hp->pairs, [hp](size_t b) { return hp->alloc(b, false); }, s, true);
         HIPC(hipEventRecord(ei[1], s));
         HIPC(hipStreamSynchronize(s));
         HIPC(hipEventElapsedTime(&ms_inter, ei[0], ei[1]));
@@ -725,7 +737,7 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
                 build_interactions(hp, s2);
                 build_pairs(hp, hp->d_slabs, (int64_t)hp->slabs.size(), N, hp->sl_ptr, hp->sl_node, hp->sl_mask,
                             hp->near_entries, hp->far_entries, hp->pairs,
-                            [hp](size_t b) { return hp->alloc(b, false); }, s2);
+                            [hp](size_t b) { return hp->alloc(b, false); }, s2, true);
                 HIPC(hipEventRecord(ei[1], s2));
                 HIPC(hipStreamSynchronize(s2));
             } catch (...) {

@@ -146,12 +146,24 @@ struct WeightSet {
     int R = 0;
 };
 
-// Evaluation work item: up to 64 targets of one source node.
+// Evaluation work item: targets of one source node (at most eval_chunk_width).
 struct Chunk {
     int32_t node;
     int32_t kind;              // 0: near (the leaf's points), 1: far (the skeleton); + 2 x instance (batch)
     int32_t first, count;      // pairs [first, first + count) of the pair lists
 };
+
+// The form of the evaluation kernel: up to 64 dimensions in FP32 precision
+// take the form that keeps the targets' split coordinates in registers (more
+// dimensions do not fit; the bf16x3 precision has its own products).
+inline bool eval_tiled(int dp, bool bf) { return dp <= 64 && !bf; }
+// Targets per chunk for a list of npairs pairs.
+int eval_chunk_width(int dp, bool bf, bool self, int64_t npairs);
+
+// Coordinate scale of the tiled form's FP16 split for the smallest bandwidth
+// hmin (vh: per-source bandwidths) and the largest squared norm of the points;
+// 0 where the scaled coordinates would leave the FP16 range.
+float eval_scale(double hmin, bool vh, float maxnorm);
 
 // (target, source node) pairs grouped by source node and kind.
 struct PairLists {
@@ -187,6 +199,7 @@ struct askit_handle {
     int minlev = 0;                    // first level whose nodes may be pruned (level restriction)
     bool varh = false;
     float maxnorm = 0.0f;              // largest FP32 squared norm of the points
+    float ev_sc = 0.0f;                // coordinate scale of the evaluation's FP16 split (0: not used)
     int device = 0;
 
     // tree (host copy; shape depends only on N and m)
@@ -375,7 +388,10 @@ void permute_weight_cols(askit_handle *h, const float *W, int64_t ldw, int rb, f
 // the requests batched with it).
 void build_pairs(const askit_handle *h, const Slab *d_slabs, int64_t nslab, int64_t ntarget, const int32_t *ptr,
                  const int32_t *node, const uint64_t *mask, int64_t ne_near, int64_t ne_far, PairLists &L,
-                 const std::function<void *(size_t)> &al, hipStream_t s, int64_t nseg = 1);
+                 const std::function<void *(size_t)> &al, hipStream_t s, bool self, int64_t nseg = 1);
+// How the tiled form holds the coordinates (eval_tile.h): 0 three bf16, 1 two
+// FP16, 2 one FP32 value each; self: the targets are the points themselves.
+int eval_mode(const askit_handle *h, bool self);
 // u at the targets Y (rows of stride dp) for the weights ws: partial sums per
 // pair slot into part (>= npairs x R floats), then per-target sums into
 // U[outmap[i]] (identity when NULL).
@@ -401,7 +417,8 @@ struct EvalInst {
     const float *Y, *Xt, *gt, *Xs, *gs;
     const int32_t *skk;
     int64_t wt_off, wsk_off;
-    int smax, dp;
+    int smax, dp, d;
+    float sc;                  // askit_handle::ev_sc
 };
 struct UpInst {
     const Node *nodes;
@@ -411,9 +428,18 @@ struct UpInst {
     int64_t wt_off, wsk_off;
     int ncol_max, smax;
 };
+// Consecutive chunks of a batch that one launch takes: the instances of one
+// padded dimension dp and coordinate form (mode) where the evaluation kernel's form
+// depends on them, else (dp above what it is built for, or bf16x3) all others
+// with their largest dp.
+struct BatchClass {
+    int64_t first, count;
+    int dp, mode;
+};
 struct BatchEvalArgs {
     const EvalInst *inst;
-    const Chunk *chunks;       // kind = 2 x instance + kind
+    const Chunk *chunks;       // kind = 2 x instance + kind; ordered by class
+    const std::vector<BatchClass> *classes;
     int64_t nchunk;
     const int32_t *tpos, *tslot;   // tpos: row in the instance's targets; tslot: batch-wide slot
     const int32_t *sbase;      // batch rows + 1
@@ -424,7 +450,7 @@ struct BatchEvalArgs {
     float *U;
     int64_t ldu;
     int R;
-    bool bf;
+    bool bf, vh;               // precision form; per-source bandwidths
     int persistent;            // 0: one workgroup per chunk; else the persistent grid size
     int32_t *queue;            // persistent: work counter (cleared by a kernel before the launch)
     int plan;                  // column passes: 0 wide (64/32 MFMA, 4/1 vector), 1 narrow (32 MFMA, 1 vector)

@@ -82,6 +82,7 @@ struct askit_batch {
     UpInst *d_uinst = nullptr;
     int2 *d_items = nullptr;
     std::vector<std::pair<int64_t, int64_t>> levels;
+    std::vector<BatchClass> classes;
     Chunk *d_chunks = nullptr;
     int32_t *d_tpos = nullptr, *d_tslot = nullptr, *d_sbase = nullptr, *d_queue = nullptr, *d_outrow = nullptr;
 
@@ -126,6 +127,7 @@ struct askit_batch {
         BatchEvalArgs a{};
         a.inst = d_einst;
         a.chunks = d_chunks;
+        a.classes = &classes;
         a.nchunk = nchunk;
         a.tpos = d_tpos;
         a.tslot = d_tslot;
@@ -139,6 +141,7 @@ struct askit_batch {
         a.ldu = ldu;
         a.R = R;
         a.bf = prm.precision == ASKIT_PREC_BF16X3;
+        a.vh = prm.bw_neighbor > 0;
         a.persistent = l.blocks > 0 ? l.blocks : 0;
         a.plan = l.plan;
         a.queue = d_queue;
@@ -385,11 +388,27 @@ askit_status askit_batch_setup(int32_t count, const float *const *X, const int64
         }
         add_offset(b->d_sbase + row_off[i], L.sbase, h->N + (i == count - 1 ? 1 : 0), (int32_t)pair_off[i]);
         einst[i] = EvalInst{h->d_nodes, h->Xt, h->Xt, h->gt, h->Xs, h->gs, h->skk, row_off[i], wsk_off[i], h->smax,
-                            h->dp};
+                            h->dp, h->d, h->ev_sc};
         uinst[i] = UpInst{h->d_nodes, h->skk, h->ncols, h->colperm, h->d_pslot, h->P, row_off[i], wsk_off[i],
                           h->ncol_max, h->smax};
     }
     b->nchunk = (int64_t)chunks.size();
+    // chunks ordered by class (instances of one class keep their order)
+    {
+        const bool bf = p->precision == ASKIT_PREC_BF16X3;
+        auto cls = [&](const Chunk &c) {
+            const askit_handle *h = b->inst[c.kind >> 1];
+            return eval_tiled(h->dp, bf) ? 4 * h->dp + eval_mode(h, true) : 1 << 20;
+        };
+        std::stable_sort(chunks.begin(), chunks.end(), [&](const Chunk &x, const Chunk &y) { return cls(x) < cls(y); });
+        for (int64_t c = 0; c < b->nchunk; ++c) {
+            const int dp = b->inst[chunks[c].kind >> 1]->dp;
+            if (c == 0 || cls(chunks[c]) != cls(chunks[c - 1]))
+                b->classes.push_back(BatchClass{c, 0, dp, eval_mode(b->inst[chunks[c].kind >> 1], true)});
+            ++b->classes.back().count;
+            b->classes.back().dp = std::max(b->classes.back().dp, dp);
+        }
+    }
     // upward items, deepest level first across all instances
     std::vector<int2> items;
     for (int lev = maxdepth; lev >= 1; --lev) {

@@ -1,8 +1,9 @@
 // Downward pass (Alg. 4) as sums over (target, source node) pairs.
 //
-// Work item: a chunk of up to 64 targets that all use one source node
-// (near: a leaf's points and weights; far: a pruned node's skeleton points
-// and skeleton weights).  Sources are taken in tiles of 64:
+// Work item: a chunk of targets that all use one source node (near: a leaf's
+// points and weights; far: a pruned node's skeleton points and skeleton
+// weights): up to 128 in the form of eval_tile.h (dp <= 64 in FP32), up to 64
+// in the form below.  Sources are taken in tiles of 64:
 //   r^2 = |x - c|^2 + |y - c|^2 - 2 (x - c).(y - c),  c = the chunk's first
 //   target: the rounding error of r^2 is a few ulps of |x - c|^2 + |y - c|^2,
 //   small where the kernel is not (a skeleton can span distant clusters, so
@@ -18,9 +19,10 @@
 // the registers, is exactly the B operand layout), 32 or 64 columns per
 // pass.  Each pair's sum goes to its own slot; a second kernel adds a
 // target's slots in order, so the result is deterministic (no atomics).
-#include "askit_impl.h"
+#include "eval_impl.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace askit {
 
@@ -40,25 +42,6 @@ constexpr int EV_T = 256;
 constexpr int EV_KC = 64;              // dimensions per LDS chunk
 constexpr int EV_LD = EV_KC + 4;       // padded LDS row (floats)
 constexpr int EV_LH = EV_KC + 8;       // padded LDS row of the bf16 operands (elements)
-
-struct ChunkParams {
-    const Chunk *chunks;
-    int64_t nchunk;
-    const int32_t *tpos, *tslot;
-    // single problem (MULTI = false)
-    const Node *nodes;
-    const float *Y, *Xt, *gt, *Xs, *gs;
-    const int32_t *skk;
-    int smax, dp;
-    // batch (MULTI = true)
-    const EvalInst *inst;
-    int32_t *queue;
-    int persistent;
-    // weights and output
-    const float *Wt, *Wsk;     // single: the problem's; batch: shared buffers (instance offsets)
-    float *part;
-    int R, r0, rb;             // columns [r0, r0 + rb) in this pass
-};
 
 // CM: columns per pass and contraction: 1 or 4 on the vector units, 32 or 64 on MFMA.
 template <int CM, bool BF, bool MULTI>
@@ -411,7 +394,7 @@ __global__ void k_zero_i32(int32_t *__restrict__ p, int n)
 }
 
 template <bool MULTI>
-static void launch_passes(ChunkParams p, bool bf, int R, int64_t grid, int32_t *queue, hipStream_t s, int c0 = 0,
+static void launch_passes(ChunkParams p, bool bf, bool vh, int R, int64_t grid, int32_t *queue, hipStream_t s, int c0 = 0,
                           int plan = 0)
 {
     // passes over columns [c0, R): plan 0 (wide) of 64, 32, 4 or 1 columns,
@@ -428,6 +411,12 @@ static void launch_passes(ChunkParams p, bool bf, int R, int64_t grid, int32_t *
             hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, queue, 1);
             HIPC(hipGetLastError());
         }
+        if (eval_tiled(p.dp, bf)) {
+            if (cm >= 32) launch_eval_tile_mat(p, cm, MULTI, vh, (unsigned)grid, s);
+            else launch_eval_tile_vec(p, cm, MULTI, vh, (unsigned)grid, s);
+            r0 += p.rb;
+            continue;
+        }
         dim3 g((unsigned)grid), b(EV_T);
 #define EV_LAUNCH(CMV)                                                                             \
     if (bf) hipLaunchKernelGGL((k_eval_chunks<CMV, true, MULTI>), g, b, 0, s, p);                 \
@@ -440,6 +429,44 @@ static void launch_passes(ChunkParams p, bool bf, int R, int64_t grid, int32_t *
         HIPC(hipGetLastError());
         r0 += p.rb;
     }
+}
+
+// The FP16 split holds |x'| <= 32768 for the scaled centred coordinates x',
+// whose size is at most twice the largest norm.  One bandwidth: s = sqrt(-2 g),
+// so that r'^2 / 2 is minus the exponent; several: a power of two (each
+// source's factor is applied afterwards), of the smallest one's size.  Below
+// 2^-14 the lower part of the split is subnormal: errors of 2^-25 in x' are
+// then far below an exponent's rounding.
+float eval_scale(double hmin, bool vh, float maxnorm)
+{
+    const double l2e = 1.4426950408889634;
+    const double s = vh ? std::exp2(std::ceil(-std::log2(hmin))) : std::sqrt(l2e) / hmin;
+    const double big = 2.0 * std::sqrt((double)maxnorm * (1.0 + 1e-5)) * s;
+    return std::isfinite(s) && s > 0.0 && s < 1e30 && s > 1e-30 && big <= 32768.0 ? (float)s : 0.0f;
+}
+
+// Up to 6 dimensions the FP32 matrix product (K = d + 2 with the norms) is both
+// the fastest (3 or 4 steps of 64 cycles against 7 bf16 steps of 32 and the
+// splitting) and the most accurate; the 16-bit forms sum 16 products at a time
+// with one truncation at the end, which costs accuracy where few dimensions
+// carry the whole of r^2: the FP16 form is taken from 13 dimensions on.  Other
+// targets than the points themselves may lie beyond the FP16 range.
+int eval_mode(const askit_handle *h, bool self)
+{
+    if (h->d <= 6) return 2;
+    return self && h->d > 12 && h->ev_sc > 0.0f ? 1 : 0;
+}
+
+// Targets per chunk.  The vector form below holds 64.  The tiled form holds
+// 256, at which a staged source row serves the most pairs, and takes fewer
+// with more source groups per target block.  A point set's own lists take 256
+// when they make enough chunks to fill the device (512 workgroups at once)
+// several times over, else 128 (twice the workgroups); queries always 128, so
+// that a request's chunks do not depend on the requests batched with it.
+int eval_chunk_width(int dp, bool bf, bool self, int64_t npairs)
+{
+    if (!eval_tiled(dp, bf)) return 64;
+    return self && npairs >= 256 * 2048 ? 256 : 128;
 }
 
 void evaluate(const askit_handle *h, const WeightSet &ws, const float *Y, const PairLists &L,
@@ -456,6 +483,9 @@ void evaluate(const askit_handle *h, const WeightSet &ws, const float *Y, const 
         p.tslot = L.tslot;
         p.nodes = h->d_nodes;
         p.Y = Y;
+        p.mode = eval_mode(h, Y == h->Xt);
+        p.sc = h->ev_sc;
+        p.d = h->d;
         p.Xt = h->Xt;
         p.gt = h->gt;
         p.Xs = h->Xs;
@@ -467,7 +497,7 @@ void evaluate(const askit_handle *h, const WeightSet &ws, const float *Y, const 
         p.Wsk = ws.Wsk;
         p.part = part;
         p.R = ws.R;
-        launch_passes<false>(p, h->prm.precision == ASKIT_PREC_BF16X3, ws.R, L.nchunk, nullptr, s);
+        launch_passes<false>(p, h->prm.precision == ASKIT_PREC_BF16X3, h->varh, ws.R, L.nchunk, nullptr, s);
     }
     const int64_t tot = L.ntarget * ws.R;
     hipLaunchKernelGGL(k_sum_slots, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, L.sbase, L.ntarget, part,
@@ -488,6 +518,9 @@ void evaluate_chunk_range(const askit_handle *h, const WeightSet &ws, const Pair
     p.tslot = L.tslot;
     p.nodes = h->d_nodes;
     p.Y = h->Xt;
+    p.mode = eval_mode(h, true);
+    p.sc = h->ev_sc;
+    p.d = h->d;
     p.Xt = h->Xt;
     p.gt = h->gt;
     p.Xs = h->Xs;
@@ -499,7 +532,7 @@ void evaluate_chunk_range(const askit_handle *h, const WeightSet &ws, const Pair
     p.Wsk = ws.Wsk;
     p.part = part;
     p.R = ws.R;
-    launch_passes<false>(p, h->prm.precision == ASKIT_PREC_BF16X3, c1, ch1 - ch0, nullptr, s, c0);
+    launch_passes<false>(p, h->prm.precision == ASKIT_PREC_BF16X3, h->varh, c1, ch1 - ch0, nullptr, s, c0);
 }
 
 void sum_slot_cols(const askit_handle *h, const PairLists &L, const float *part, int R, int c0, int rb,
@@ -514,20 +547,22 @@ void sum_slot_cols(const askit_handle *h, const PairLists &L, const float *part,
 void evaluate_batch(const BatchEvalArgs &b, hipStream_t s)
 {
     if (b.rows == 0) return;
-    if (b.nchunk > 0) {
-        ChunkParams p{};
-        p.chunks = b.chunks;
-        p.nchunk = b.nchunk;
-        p.tpos = b.tpos;
-        p.tslot = b.tslot;
-        p.inst = b.inst;
-        p.persistent = b.persistent > 0;
-        p.Wt = b.Wt;
-        p.Wsk = b.Wsk;
-        p.part = b.part;
-        p.R = b.R;
-        const int64_t grid = p.persistent ? std::min<int64_t>(b.persistent, b.nchunk) : b.nchunk;
-        launch_passes<true>(p, b.bf, b.R, grid, b.queue, s, 0, b.plan);
+    ChunkParams p{};
+    p.tpos = b.tpos;
+    p.tslot = b.tslot;
+    p.inst = b.inst;
+    p.persistent = b.persistent > 0;
+    p.Wt = b.Wt;
+    p.Wsk = b.Wsk;
+    p.part = b.part;
+    p.R = b.R;
+    for (const BatchClass &c : *b.classes) {
+        p.chunks = b.chunks + c.first;
+        p.nchunk = c.count;
+        p.dp = c.dp;
+        p.mode = c.mode;
+        const int64_t grid = p.persistent ? std::min<int64_t>(b.persistent, c.count) : c.count;
+        launch_passes<true>(p, b.bf, b.vh, b.R, grid, b.queue, s, 0, b.plan);
     }
     const int64_t tot = b.rows * b.R;
     hipLaunchKernelGGL(k_sum_slots, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, b.sbase, b.rows, b.part,

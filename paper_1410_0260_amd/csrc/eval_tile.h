@@ -1,0 +1,598 @@
+// Evaluation of chunks of up to 256 targets of one source node, dp <= 64,
+// FP32 precision: the kernel template of eval_vec.hip and eval_mat.hip.
+//
+// The pairwise term r^2 = |x - c|^2 + |y - c|^2 - 2 (x - c).(y - c) comes from
+// the matrix cores with at least FP32's precision.  A centred coordinate x',
+// scaled so that r'^2 / 2 is minus the exponent, is held as
+//   FP16: two FP16 values h + l, within 2^-24 of x'; products hl, lh, hh;
+//   BF16: three bf16 values h + m + l, exactly x'; products lh, hl, mm, mh, hm,
+//         hh (below the FP16 range's ends, see eval_scale, or d <= 12);
+//   FP32: itself (d <= 6);
+// the dropped products are below 2^-24 of |x'||y'|, the size of one FP32
+// rounding, and c, the mean of 8 targets, halves |x'|^2 + |y'|^2 against one of
+// them.  Measured against 64 bits (2000 points, kernel widths from 0.06 sqrt(d)
+// to 4 sqrt(d) and per source, d = 2 .. 64), the sums' error is 0.4 to 1.0 times
+// that of v_mfma_f32_32x32x2_f32 on coordinates centred at the first target.
+// One more bf16 product adds -|x'|^2/2 and -|y'|^2/2, split against ones, so the
+// accumulator is the exponent and a kernel value costs one exp2 (clamped to 1)
+// and its contraction (per-source bandwidths: one multiply more).
+//
+// What bounds it: at dp = 64 a 32 x 32 block takes 13 matrix steps = 416
+// cycles (FP32: 2048) and about 110 vector instructions, 16 of them exp2; the
+// matrix pipe is busy 36% and the vector pipe 47% of the time, the rest is
+// latency at 4 waves per SIMD.  Hence the split:
+//   - up to 256 targets per workgroup of 8 waves, every wave one block of 32
+//     targets and all sources: a staged source row (centring, splitting, norm)
+//     serves 256 targets; fewer targets leave more source groups per block;
+//   - the targets' split coordinates stay in registers for the whole chunk (8
+//     or 12 registers per 16 dimensions): LDS serves the source operand only;
+//   - the next tile's rows are loaded while the current one is computed, and
+//     (vector form) staged into the other of two LDS buffers: one barrier per
+//     tile.  Two blocks in flight per wave spilled and were slower (1.31
+//     against 0.96 ms at 2^18 x 64, one column).
+// 2^20 x 64, one column: 15.7 -> 5.0 ms per evaluation (update included 16.6
+// -> 5.9); 2^18 points, update included: 64 columns 9.4 -> 5.0 ms (d = 64),
+// one column 3.06 -> 0.96 (d = 64), 1.60 -> 0.43 (d = 16), 1.50 -> 0.49 (d = 4).
+#pragma once
+
+#include "eval_impl.h"
+
+namespace askit {
+
+typedef __attribute__((ext_vector_type(16))) float ev_f32x16;
+typedef __attribute__((ext_vector_type(2))) float ev_f32x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 ev_bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 ev_bf16x2;
+typedef __attribute__((ext_vector_type(8))) _Float16 ev_f16x8;
+typedef __attribute__((ext_vector_type(2))) _Float16 ev_f16x2;
+
+// how a kernel's coordinates are held: three bf16, two FP16 or one FP32 value
+enum { EV_BF16 = 0, EV_F16 = 1, EV_F32 = 2 };
+
+constexpr int ET_T = 512;                 // threads
+constexpr int ET_NT = 256;                // targets per chunk, at most
+
+__device__ __forceinline__ uint32_t et_pk(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(ev_f32x2{a, b}, ev_bf16x2));
+}
+
+// (a, b) as three packed bf16 pairs whose sums are a and b exactly.  The
+// remainders come from the two-term dot product a - 1 h_a + 0 h_b (exact:
+// the difference is a float), one instruction instead of an unpack and a
+// subtraction.  The pairs (-1, 0) and (0, -1) are kept opaque: as inline
+// constants they would be read as FP32 bits.
+__device__ __forceinline__ void et_split3(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    uint32_t ulo, uhi;
+    asm("s_mov_b32 %0, 0xbf80" : "=s"(ulo));
+    asm("s_mov_b32 %0, 0xbf800000" : "=s"(uhi));
+    const ev_bf16x2 lo = __builtin_bit_cast(ev_bf16x2, ulo), hi = __builtin_bit_cast(ev_bf16x2, uhi);
+    h = et_pk(a, b);
+    a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ev_bf16x2, h), lo, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ev_bf16x2, h), hi, b, false);
+    m = et_pk(a, b);
+    a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ev_bf16x2, m), lo, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ev_bf16x2, m), hi, b, false);
+    l = et_pk(a, b);
+}
+
+// (a, b) as two packed FP16 pairs, within 2^-24 of each (the second rounds
+// the first's remainder to nearest)
+__device__ __forceinline__ void et_split2(float a, float b, uint32_t &h, uint32_t &l)
+{
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector(ev_f32x2{a, b}, ev_f16x2));
+    float ra, rb;                              // a - h_a, b - h_b
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(h), "v"(a));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(h), "v"(b));
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(ev_f32x2{ra, rb}, ev_f16x2));
+}
+
+// one matrix step on operand registers holding bf16 or FP16 values
+template <bool F16>
+__device__ __forceinline__ ev_f32x16 et_mfma(uint4 a, uint4 b, ev_f32x16 c)
+{
+    if constexpr (F16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(ev_f16x8, a), __builtin_bit_cast(ev_f16x8, b),
+                                                      c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(ev_bf16x8, a),
+                                                       __builtin_bit_cast(ev_bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ uint4 et_lds(const void *p) { return *reinterpret_cast<const uint4 *>(p); }
+
+// sum over aligned groups of 4 or 8 lanes (every lane of the group gets it)
+template <int W>
+__device__ __forceinline__ float et_group_sum(float v)
+{
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    v += dpp(v, std::integral_constant<int, 0xb1>{});           // quad_perm [1,0,3,2]
+    v += dpp(v, std::integral_constant<int, 0x4e>{});           // quad_perm [2,3,0,1]
+    if constexpr (W == 8) v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    return v;
+}
+
+// Power of two the coordinates are scaled by: 1 for bandwidths within
+// 2^-40 .. 2^40, else what brings them there (products of the smallest split
+// parts then stay far from the denormal range, which the matrix cores flush).
+__device__ __forceinline__ int et_scale_log2(float g0)
+{
+    const int e = (int)((__float_as_uint(g0) >> 23) & 0xff);
+    if (e == 0 || e == 255) return 0;
+    const int k = (e - 126) / 2;                                  // about log2(1 / h)
+    return k > 40 ? k - 40 : k < -40 ? k + 40 : 0;
+}
+
+template <int KS, int CM, int MODE>
+struct EvTile {
+    static constexpr bool F32 = MODE == EV_F32;
+    static constexpr int NP = MODE == EV_F16 ? 2 : 3;                     // split parts of a coordinate
+    static constexpr bool MC = CM >= 32;
+    static constexpr int DPU = F32 ? 8 : (KS == 1 || (MC && KS == 2)) ? 4 : 8;   // dimensions per staging thread
+    static constexpr int UPR = F32 ? 1 : (KS == 1 || (!MC && KS == 2)) ? 4 : 8;  // staging threads per source row
+    static constexpr int ST = MC ? 64 : F32 ? (CM == 1 ? 256 : 128) : ET_T / UPR;   // source rows per tile
+    static constexpr int LDX = 16 * KS + 8;    // row stride of the split operands: 16-byte reads of 16 rows
+                                               // fall into distinct banks for every KS
+    static constexpr int NQ = MC ? CM / 32 : 1;
+    static constexpr int NBUF = MC ? 1 : 2;
+    // bytes of one buffer: split rows, norms, factors, weights
+    static constexpr int OFF_N = F32 ? ST * 32 : NP * ST * LDX * 2;
+    static constexpr int OFF_G = OFF_N + (F32 ? 0 : ST * 16);
+    static constexpr int OFF_W = OFF_G + ST * 4;
+    static constexpr int WPART = ST * NQ * 64;                            // one split part of the weight operand
+    static constexpr int BYTES = OFF_W + (MC ? 3 * WPART : ST * CM * 4);
+    static constexpr int RED = MC ? ET_NT * 33 * 4 : ET_NT * CM * 4;
+    static constexpr int WPE = (MC ? KS >= 2 : CM == 4 && KS >= 3) ? 2 : 4;                   // waves per SIMD
+    static constexpr int LDS = NBUF * BYTES > RED ? NBUF * BYTES : RED;
+};
+
+struct EvView {                               // one chunk's arrays
+    const float *Y, *src, *g, *w;
+    int ns;
+    float sc;                                 // FP16 form: coordinate scale
+    int d;
+};
+
+template <int KS, int CM, bool VH, int MODE>
+__device__ __forceinline__ void ev_tile(const ChunkParams &p, const Chunk &ch, const EvView &v, char *lds)
+{
+    using E = EvTile<KS, CM, MODE>;
+    constexpr bool F16 = MODE == EV_F16, F32 = MODE == EV_F32;
+    constexpr bool MC = E::MC;
+    constexpr int ST = E::ST, DPU = E::DPU, UPR = E::UPR, LDX = E::LDX, NQ = E::NQ, DP = 16 * KS, NP = E::NP;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int nt = ch.count, ns = v.ns;
+    // waves: target blocks of 32 x source groups; few targets: more source groups
+    const int tbl = nt > 128 ? 3 : MC || nt > 64 ? 2 : nt > 32 ? 1 : 0;   // log2 of the target blocks
+    const int tq = 32 * (wv & ((1 << tbl) - 1)), sg = wv >> tbl, nsg = 8 >> tbl;
+
+    const int32_t *tp = p.tpos + ch.first;
+    // coordinates times s: one bandwidth: r'^2 = s^2 r^2 is minus the exponent
+    const float g0 = v.g[0];
+    const float sc = F16 ? v.sc : VH ? ldexpf(1.0f, et_scale_log2(g0)) : sqrtf(-2.0f * g0);
+    const float q2 = VH ? -2.0f / (sc * sc) : 0.0f;
+
+    // ---- centre (scaled): the mean of 8 of the targets.  The rounding error
+    // of r^2 is a few ulps of |x - c|^2 + |y - c|^2, so c sits amid the targets.
+    float *cent = reinterpret_cast<float *>(lds);
+    if (tid < DP) {
+        float c = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c += v.Y[(int64_t)tp[(nt - 1) * j / 7] * DP + tid];
+        cent[tid] = 0.125f * c * sc;
+    }
+    // this wave's targets
+    float y[KS][8];
+    {
+        const float *yr = v.Y + (int64_t)tp[min(tq + l32, nt - 1)] * DP + 8 * half;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            *reinterpret_cast<float4 *>(y[s]) = *reinterpret_cast<const float4 *>(yr + 16 * s);
+            *reinterpret_cast<float4 *>(y[s] + 4) = *reinterpret_cast<const float4 *>(yr + 16 * s + 4);
+        }
+    }
+    __syncthreads();
+    // ---- the targets split, in registers
+    uint4 bt[KS][NP], bx;
+    float bf[4];
+    if constexpr (F32) {
+        // k = 2 j + half of the row (y0 .. y5, 1, -|y|^2 / 2)
+        float c[8], t[8], tn = 0.0f;
+        const float *yr = v.Y + (int64_t)tp[min(tq + l32, nt - 1)] * DP;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            c[j] = cent[j];
+            t[j] = fmaf(yr[j], sc, -c[j]);
+            tn = fmaf(t[j], t[j], tn);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) bf[j] = half ? t[2 * j + 1] : t[2 * j];
+        bf[3] = half ? -0.5f * tn : 1.0f;
+    } else {
+        float tn = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            float c[8];
+            *reinterpret_cast<float4 *>(c) = *reinterpret_cast<const float4 *>(cent + 16 * s + 8 * half);
+            *reinterpret_cast<float4 *>(c + 4) = *reinterpret_cast<const float4 *>(cent + 16 * s + 8 * half + 4);
+            uint32_t u[3][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                y[s][j] = fmaf(y[s][j], sc, -c[j]);
+                tn = fmaf(y[s][j], y[s][j], tn);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (F16) et_split2(y[s][2 * j], y[s][2 * j + 1], u[0][j], u[1][j]);
+                else et_split3(y[s][2 * j], y[s][2 * j + 1], u[0][j], u[1][j], u[2][j]);
+            }
+#pragma unroll
+            for (int q = 0; q < NP; ++q) bt[s][q] = uint4{u[q][0], u[q][1], u[q][2], u[q][3]};
+        }
+        tn += __shfl_xor(tn, 32);
+        // against the source rows' (sh, sm, sl, 1, 1, 1, 0, 0)
+        uint32_t h, m, l;
+        et_split3(-0.5f * tn, 0.0f, h, m, l);
+        bx = half ? uint4{0u, 0u, 0u, 0u} : uint4{0x3f803f80u, 0x3f80u | (h << 16), (m & 0xffffu) | (l << 16), 0u};
+    }
+
+    // ---- staging: this thread's part of a source row, its centre coordinates
+    const int srow = tid / UPR, so = tid % UPR, sd = so * DPU;
+    const bool son = srow < ST && sd < DP;
+    float cs[DPU], px[DPU], pg = 0.0f;
+#pragma unroll
+    for (int j = 0; j < DPU; ++j) {
+        cs[j] = son ? cent[sd + j] : 0.0f;
+        px[j] = 0.0f;
+    }
+    __syncthreads();                          // the centre's place is the first buffer's
+    // weights: vector form one entry per thread; matrix form 8 sources of one
+    // column, in the order the kernel tile's registers hold them
+    constexpr int NW = MC ? 8 : 1;
+    float pw[NW];
+    const int we_r = MC ? 0 : (tid / CM) % ST, we_c = MC ? 0 : tid % CM;
+    const int wc = MC ? tid % CM : 0, wg = MC ? tid / CM : 0;             // column, group (16 sources, half)
+    static_assert(!MC || ST / 8 * CM <= ET_T, "one weight unit per thread");
+    const bool won = MC ? tid < ST / 8 * CM : tid < ST * CM;
+    auto fetch = [&](int s1) {
+        const int n1 = min(ST, ns - s1);
+        if (son) {
+            const float *x = v.src + (int64_t)(s1 + min(srow, n1 - 1)) * DP + sd;
+#pragma unroll
+            for (int j = 0; j < DPU; j += 4)
+                *reinterpret_cast<float4 *>(px + j) = *reinterpret_cast<const float4 *>(x + j);
+            if constexpr (VH) pg = v.g[s1 + min(srow, n1 - 1)];
+        }
+        if (won) {
+            if constexpr (MC) {
+                const int64_t c = p.r0 + min(wc, p.rb - 1);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int r = 16 * (wg >> 1) + 8 * (j / 4) + 4 * (wg & 1) + j % 4;
+                    pw[j] = v.w[(int64_t)(s1 + min(r, n1 - 1)) * p.R + c];
+                }
+            } else {
+                pw[0] = v.w[(int64_t)(s1 + min(we_r, n1 - 1)) * p.R + p.r0 + min(we_c, p.rb - 1)];
+            }
+        }
+    };
+    auto stage = [&](char *buf, int nsrc) {
+        if (srow < ST) {
+            float x[DPU], sn = 0.0f;
+#pragma unroll
+            for (int j = 0; j < DPU; ++j) {
+                x[j] = fmaf(px[j], sc, -cs[j]);
+                sn = fmaf(x[j], x[j], sn);
+            }
+            if constexpr (F32) {
+                float4 *d = reinterpret_cast<float4 *>(buf) + srow;
+                d[0] = float4{x[0], x[2], x[4], -0.5f * sn};
+                d[ST] = float4{x[1], x[3], x[5], 1.0f};
+                if constexpr (VH) reinterpret_cast<float *>(buf + E::OFF_G)[srow] = q2 * pg;
+            } else {
+            uint32_t u[3][DPU / 2];
+#pragma unroll
+            for (int j = 0; j < DPU / 2; ++j) {
+                if constexpr (F16) et_split2(x[2 * j], x[2 * j + 1], u[0][j], u[1][j]);
+                else et_split3(x[2 * j], x[2 * j + 1], u[0][j], u[1][j], u[2][j]);
+            }
+            if (son) {
+                uint16_t *d = reinterpret_cast<uint16_t *>(buf) + srow * LDX + sd;
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    if constexpr (DPU == 8)
+                        *reinterpret_cast<uint4 *>(d + q * ST * LDX) = uint4{u[q][0], u[q][1], u[q][2], u[q][3]};
+                    else
+                        *reinterpret_cast<uint2 *>(d + q * ST * LDX) = uint2{u[q][0], u[q][1]};
+                }
+            }
+            sn = et_group_sum<UPR>(sn);
+            if (so == 0) {
+                uint32_t h, m, l;
+                et_split3(-0.5f * sn, 0.0f, h, m, l);
+                *reinterpret_cast<uint4 *>(buf + E::OFF_N + 16 * srow) =
+                    uint4{(h & 0xffffu) | (m << 16), (l & 0xffffu) | 0x3f800000u, 0x3f803f80u, 0u};
+                if constexpr (VH) reinterpret_cast<float *>(buf + E::OFF_G)[srow] = q2 * pg;   // > 0: the exponent is acc times it
+            }
+            }
+        }
+        if (won) {
+            if constexpr (MC) {
+                uint32_t uh[4], um[4], ul[4];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int r = 16 * (wg >> 1) + 8 * (j / 4) + 4 * (wg & 1) + j % 4;
+                    pw[j] = (r < nsrc && wc < p.rb) ? pw[j] : 0.0f;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) et_split3(pw[2 * j], pw[2 * j + 1], uh[j], um[j], ul[j]);
+                char *d = buf + E::OFF_W + 16 * (((wg >> 1) * NQ + wc / 32) * 64 + 32 * (wg & 1) + wc % 32);
+                *reinterpret_cast<uint4 *>(d) = uint4{uh[0], uh[1], uh[2], uh[3]};
+                *reinterpret_cast<uint4 *>(d + E::WPART) = uint4{um[0], um[1], um[2], um[3]};
+                *reinterpret_cast<uint4 *>(d + 2 * E::WPART) = uint4{ul[0], ul[1], ul[2], ul[3]};
+            } else {
+                reinterpret_cast<float *>(buf + E::OFF_W)[tid] = (we_r < nsrc && we_c < p.rb) ? pw[0] : 0.0f;
+            }
+        }
+    };
+
+    ev_f32x16 uacc[NQ];
+    float vacc[MC ? 1 : CM];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) uacc[q] = ev_f32x16{};
+#pragma unroll
+    for (int j = 0; j < (MC ? 1 : CM); ++j) vacc[j] = 0.0f;
+
+    if (ns > 0) fetch(0);
+    int ib = 0;
+    for (int s0 = 0; s0 < ns; s0 += ST) {
+        const int nsrc = min(ST, ns - s0);
+        char *buf = lds + ib * E::BYTES;
+        if constexpr (E::NBUF == 1) __syncthreads();       // the previous tile's reads are done
+        stage(buf, nsrc);
+        // two buffers: this one was last read for the tile before the
+        // previous, and every wave has passed the previous tile's barrier since
+        __syncthreads();
+        if (s0 + ST < ns) fetch(s0 + ST);
+        // products of block b (the small ones first: the sums at full magnitude
+        // are KS only), then the norms: acc = -r'^2 / 2
+        auto products = [&](int b) -> ev_f32x16 {
+            const uint16_t *pa = reinterpret_cast<const uint16_t *>(buf) + (32 * b + l32) * LDX + 8 * half;
+            ev_f32x16 acc = {};
+            if constexpr (F32) {
+                const float4 a = reinterpret_cast<const float4 *>(buf)[half * ST + 32 * b + l32];
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bf[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bf[1], acc, 0, 0, 0);
+                if (v.d > 4) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bf[2], acc, 0, 0, 0);
+                return __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bf[3], acc, 0, 0, 0);
+            }
+            uint4 ah[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                ah[s] = et_lds(pa + 16 * s);
+                const uint4 al = et_lds(pa + (NP - 1) * ST * LDX + 16 * s);
+                acc = et_mfma<F16>(al, bt[s][0], acc);
+                acc = et_mfma<F16>(ah[s], bt[s][NP - 1], acc);
+                if constexpr (!F16) {
+                    const uint4 am = et_lds(pa + ST * LDX + 16 * s);
+                    acc = et_mfma<F16>(am, bt[s][1], acc);
+                    acc = et_mfma<F16>(am, bt[s][0], acc);
+                    acc = et_mfma<F16>(ah[s], bt[s][1], acc);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s) acc = et_mfma<F16>(ah[s], bt[s][0], acc);
+            acc = et_mfma<false>(et_lds(buf + E::OFF_N + 16 * (32 * b + l32)), bx, acc);
+            return acc;
+        };
+        auto contract = [&](int b, const ev_f32x16 &acc) {
+            // lane = target tq + l32, register r = source 32 b + 8 (r / 4) + 4 half + r % 4
+            float kv[16];
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                float gg[4];
+                if constexpr (VH)
+                    *reinterpret_cast<float4 *>(gg) =
+                        *reinterpret_cast<const float4 *>(buf + E::OFF_G + 4 * (32 * b + 8 * r4 + 4 * half));
+                // the hardware 2^x, its result clamped to [0, 1] (a rounding
+                // error may leave r^2 below 0): values below 2^-126 (flushed)
+                // are far below any sum's rounding
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float e = VH ? acc[4 * r4 + j] * gg[j] : acc[4 * r4 + j];
+                    kv[4 * r4 + j] = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(e), 0.0f, 1.0f);
+                }
+            }
+            if constexpr (MC) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    uint32_t uh[4], um[4], ul[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        et_split3(kv[8 * t + 2 * j], kv[8 * t + 2 * j + 1], uh[j], um[j], ul[j]);
+                    const uint4 kh{uh[0], uh[1], uh[2], uh[3]}, km{um[0], um[1], um[2], um[3]},
+                        kl{ul[0], ul[1], ul[2], ul[3]};
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        const char *d = buf + E::OFF_W + 16 * (((2 * b + t) * NQ + q) * 64 + lane);
+                        const uint4 wh = et_lds(d), wm = et_lds(d + E::WPART), wl = et_lds(d + 2 * E::WPART);
+                        uacc[q] = et_mfma<false>(wl, kh, uacc[q]);
+                        uacc[q] = et_mfma<false>(wh, kl, uacc[q]);
+                        uacc[q] = et_mfma<false>(wm, km, uacc[q]);
+                        uacc[q] = et_mfma<false>(wm, kh, uacc[q]);
+                        uacc[q] = et_mfma<false>(wh, km, uacc[q]);
+                        uacc[q] = et_mfma<false>(wh, kh, uacc[q]);
+                    }
+                }
+            } else {
+                const float *pwt = reinterpret_cast<const float *>(buf + E::OFF_W);
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const float4 *w4 = reinterpret_cast<const float4 *>(pwt + CM * (32 * b + 8 * r4 + 4 * half));
+                    if constexpr (CM == 1) {
+                        const float4 w = w4[0];
+                        vacc[0] = fmaf(kv[4 * r4], w.x, vacc[0]);
+                        vacc[0] = fmaf(kv[4 * r4 + 1], w.y, vacc[0]);
+                        vacc[0] = fmaf(kv[4 * r4 + 2], w.z, vacc[0]);
+                        vacc[0] = fmaf(kv[4 * r4 + 3], w.w, vacc[0]);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float4 w = w4[j];
+                            vacc[0] = fmaf(kv[4 * r4 + j], w.x, vacc[0]);
+                            vacc[1] = fmaf(kv[4 * r4 + j], w.y, vacc[1]);
+                            vacc[2] = fmaf(kv[4 * r4 + j], w.z, vacc[2]);
+                            vacc[3] = fmaf(kv[4 * r4 + j], w.w, vacc[3]);
+                        }
+                    }
+                }
+            }
+        };
+        for (int b = sg; 32 * b < nsrc; b += nsg) contract(b, products(b));
+        if constexpr (E::NBUF == 2) ib ^= 1;
+    }
+
+    // ---- the source groups' sums of each target, then one sum per slot
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(lds);
+    if constexpr (MC) {
+        // 32 columns at a time through LDS, so that a slot's columns are
+        // written together
+        const int t = tq + l32, col = tid & 31;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (q > 0) __syncthreads();
+            if (sg == 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[t * 33 + 8 * (r / 4) + 4 * half + r % 4] = uacc[q][r];
+            }
+            __syncthreads();
+            if (nsg > 1) {
+                if (sg == 1) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[t * 33 + 8 * (r / 4) + 4 * half + r % 4] += uacc[q][r];
+                }
+                __syncthreads();
+            }
+            if (32 * q + col < p.rb)
+                for (int i = tid / 32; i < nt; i += ET_T / 32)
+                    p.part[(int64_t)p.tslot[ch.first + i] * p.R + p.r0 + 32 * q + col] = red[i * 33 + col];
+        }
+    } else {
+        const int ntb = 32 << tbl;                       // targets held (>= nt)
+#pragma unroll
+        for (int j = 0; j < CM; ++j) {
+            vacc[j] += __shfl_xor(vacc[j], 32);          // the two source halves
+            if (half == 0) red[(sg * ntb + tq + l32) * CM + j] = vacc[j];
+        }
+        __syncthreads();
+        for (int e = tid; e < nt * CM; e += ET_T) {
+            const int i = e / CM, j = e % CM;
+            float u = red[e];
+            for (int q = 1; q < nsg; ++q) u += red[q * ntb * CM + e];
+            if (j < p.rb) p.part[(int64_t)p.tslot[ch.first + i] * p.R + p.r0 + j] = u;
+        }
+    }
+}
+
+// One workgroup per chunk (all of dp = 16 KS); MULTI: the chunk's instance
+// gives its arrays, and a persistent grid takes chunks from a queue.
+template <int KS, int CM, bool VH, int MODE, bool MULTI>
+__global__ __launch_bounds__(ET_T, (EvTile<KS, CM, MODE>::WPE)) void k_eval_tile(ChunkParams p)
+{
+    __shared__ __attribute__((aligned(16))) char lds[EvTile<KS, CM, MODE>::LDS];
+    auto process = [&](int64_t ci) {
+        const Chunk ch = p.chunks[ci];
+        const int a = ch.node;
+        const Node *nodes = p.nodes;
+        const float *Xt = p.Xt, *gt = p.gt, *Xs = p.Xs, *gs = p.gs, *Wt = p.Wt, *Wsk = p.Wsk;
+        const int32_t *skk = p.skk;
+        int smax = p.smax;
+        constexpr int DP = 16 * KS;
+        EvView v;
+        v.Y = p.Y;
+        v.sc = p.sc;
+        v.d = p.d;
+        if constexpr (MULTI) {
+            const EvalInst &I = p.inst[ch.kind >> 1];
+            nodes = I.nodes;
+            v.Y = I.Y;
+            v.sc = I.sc;
+            v.d = I.d;
+            Xt = I.Xt;
+            gt = I.gt;
+            Xs = I.Xs;
+            gs = I.gs;
+            skk = I.skk;
+            smax = I.smax;
+            Wt = p.Wt + I.wt_off * p.R;
+            Wsk = p.Wsk + I.wsk_off * p.R;
+        }
+        if ((ch.kind & 1) == 0) {
+            const Node nd = nodes[a];
+            v.ns = nd.hi - nd.lo;
+            v.src = Xt + (int64_t)nd.lo * DP;
+            v.g = gt + nd.lo;
+            v.w = Wt + (int64_t)nd.lo * p.R;
+        } else {
+            v.ns = skk[a];
+            v.src = Xs + (int64_t)a * smax * DP;
+            v.g = gs + (int64_t)a * smax;
+            v.w = Wsk + (int64_t)a * smax * p.R;
+        }
+        ev_tile<KS, CM, VH, MODE>(p, ch, v, lds);
+    };
+    if constexpr (!MULTI) {
+        process(blockIdx.x);
+    } else {
+        // one call site (inlined): the block's own chunk, or the queue's next
+        __shared__ int64_t item;
+        int64_t i = blockIdx.x;
+        for (;;) {
+            if (p.persistent) {
+                __syncthreads();    // the previous item is done with the shared buffers
+                if (threadIdx.x == 0) item = atomicAdd(p.queue, 1);
+                __syncthreads();
+                i = item;
+            }
+            if (i >= p.nchunk) break;
+            process(i);
+            if (!p.persistent) break;
+        }
+    }
+}
+
+template <int CM, bool VH, int MODE, bool MULTI>
+static inline void launch_eval_tile4(const ChunkParams &p, unsigned grid, hipStream_t s)
+{
+    const dim3 g(grid), b(ET_T);
+    if (p.dp == 16) hipLaunchKernelGGL((k_eval_tile<1, CM, VH, MODE, MULTI>), g, b, 0, s, p);
+    else if constexpr (MODE == EV_F32) fail(ASKIT_ERR_UNSUPPORTED, "evaluation tile of another dimension");
+    else if (p.dp == 32) hipLaunchKernelGGL((k_eval_tile<2, CM, VH, MODE, MULTI>), g, b, 0, s, p);
+    else if (p.dp == 48) hipLaunchKernelGGL((k_eval_tile<3, CM, VH, MODE, MULTI>), g, b, 0, s, p);
+    else if (p.dp == 64) hipLaunchKernelGGL((k_eval_tile<4, CM, VH, MODE, MULTI>), g, b, 0, s, p);
+    else fail(ASKIT_ERR_UNSUPPORTED, "evaluation tile of another dimension");
+    HIPC(hipGetLastError());
+}
+
+template <int CM, int MODE>
+static inline void launch_eval_tile2(const ChunkParams &p, bool multi, bool vh, unsigned grid, hipStream_t s)
+{
+    if (multi && vh) launch_eval_tile4<CM, true, MODE, true>(p, grid, s);
+    else if (multi) launch_eval_tile4<CM, false, MODE, true>(p, grid, s);
+    else if (vh) launch_eval_tile4<CM, true, MODE, false>(p, grid, s);
+    else launch_eval_tile4<CM, false, MODE, false>(p, grid, s);
+}
+
+template <int CM>
+static inline void launch_eval_tile(const ChunkParams &p, bool multi, bool vh, unsigned grid, hipStream_t s)
+{
+    if (p.mode == EV_F32) launch_eval_tile2<CM, EV_F32>(p, multi, vh, grid, s);
+    else if (p.mode == EV_F16) launch_eval_tile2<CM, EV_F16>(p, multi, vh, grid, s);
+    else launch_eval_tile2<CM, EV_BF16>(p, multi, vh, grid, s);
+}
+
+}  // namespace askit

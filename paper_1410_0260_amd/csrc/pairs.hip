@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64) void k_pair_fill(const Slab *__restrict__ slabs
 
 void build_pairs(const askit_handle *h, const Slab *d_slabs, int64_t nslab, int64_t ntarget, const int32_t *ptr,
                  const int32_t *node, const uint64_t *mask, int64_t ne_near, int64_t ne_far, PairLists &L,
-                 const std::function<void *(size_t)> &al, hipStream_t s, int64_t nseg)
+                 const std::function<void *(size_t)> &al, hipStream_t s, bool self, int64_t nseg)
 {
     const int64_t ne = ne_near + ne_far;
     const int64_t nn = (int64_t)h->nodes.size();
@@ -234,18 +234,21 @@ void build_pairs(const askit_handle *h, const Slab *d_slabs, int64_t nslab, int6
         hipLaunchKernelGGL(k_scatter_off, dim3(g), dim3(256), 0, s, idx_s, off_s, ne, off_e);
         HIPC(hipGetLastError());
     }
-    // host: pair total and the chunk table (64 targets of one source per chunk)
+    // host: pair total and the chunk table (targets of one source per chunk)
     std::vector<int32_t> hc(nkey);
     HIPC(hipMemcpyAsync(hc.data(), cnt, sizeof(int32_t) * nkey, hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
+    int64_t total = 0;
+    for (int64_t k = 0; k < nkey; ++k) total += hc[k];
+    const int64_t cw = eval_chunk_width(h->dp, h->prm.precision == ASKIT_PREC_BF16X3, self, total);
     int64_t npairs = 0;
     std::vector<Chunk> chunks;
     L.near_lists = L.far_lists = 0;
     for (int64_t k = 0; k < nkey; ++k) {
         (k & 1 ? L.far_lists : L.near_lists) += hc[k];
-        for (int64_t j = 0; j < hc[k]; j += 64)
+        for (int64_t j = 0; j < hc[k]; j += cw)
             chunks.push_back(Chunk{(int32_t)((k >> 1) % nn), (int32_t)(k & 1), (int32_t)(npairs + j),
-                                   (int32_t)std::min<int64_t>(64, hc[k] - j)});
+                                   (int32_t)std::min<int64_t>(cw, hc[k] - j)});
         npairs += hc[k];
     }
     if (npairs >= (1ll << 31)) fail(ASKIT_ERR_UNSUPPORTED, "more than 2^31 (target, source) pairs");
