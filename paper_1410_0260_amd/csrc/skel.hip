@@ -174,27 +174,24 @@ constexpr int QR_T = 1024;
 constexpr int QR_MAXCOL = 2048;
 constexpr int QR_MAXROW = 1024;
 
-// Lane l's value from lane l ^ o (o = 8, 4, 2, 1; the partner is always in
-// the same group of 16): xor 8 and 4 by a swizzle in the LDS crossbar, xor 2
-// and 1 by DPP quad permutes, so no LDS address round trip.
+// DPP moves within a row of 16 lanes (no LDS round trip): O = 8 and 4 rotate
+// the row by 8 and 4 lanes, 2 and 1 are the quad permutes lane ^ 2 and lane ^ 1.
+// Applied to partial results over the partners so far, in this order, each
+// leaves every lane with the combination over twice as many lanes.
+template <int O>
+__device__ __forceinline__ int32_t row_move(int32_t v)
+{
+    constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4e : 0xb1;
+    return __builtin_amdgcn_mov_dpp(v, ctrl, 0xf, 0xf, false);
+}
 template <int O>
 __device__ __forceinline__ double xor_lane(double v)
 {
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    if constexpr (O == 8 || O == 4) {
-        constexpr int pat = 0x1f | (O << 10);          // and 31, or 0, xor O
-        lo = __builtin_amdgcn_ds_swizzle(lo, pat);
-        hi = __builtin_amdgcn_ds_swizzle(hi, pat);
-    } else {
-        constexpr int ctrl = O == 2 ? 0x4e : 0xb1;     // quad_perm [2,3,0,1] / [1,0,3,2]
-        lo = __builtin_amdgcn_mov_dpp(lo, ctrl, 0xf, 0xf, false);
-        hi = __builtin_amdgcn_mov_dpp(hi, ctrl, 0xf, 0xf, false);
-    }
-    return __hiloint2double(hi, lo);
+    return __hiloint2double(row_move<O>(__double2hiint(v)), row_move<O>(__double2loint(v)));
 }
 
-// Sum over a group of 16 lanes by the xor butterfly: every lane of the group
-// ends with the same value.
+// Sum over a group of 16 lanes: every lane of the group ends with the same
+// value (the rotations combine the lanes a xor butterfly would).
 __device__ __forceinline__ double group16_sum(double v)
 {
     v += xor_lane<8>(v);
@@ -387,9 +384,16 @@ struct GangSlot {
     int32_t seq, pad;
 };
 
-__device__ __forceinline__ bool qg_better(double v1, int p1, double v2, int p2)
+struct QrBest {
+    double v;
+    int32_t key;                              // position << 16 | column
+};
+
+__device__ __forceinline__ void qr_take(QrBest &b, double v, int32_t key)
 {
-    return v1 > v2 || (v1 == v2 && p1 < p2);
+    const bool better = v > b.v || (v == b.v && key < b.key);
+    b.v = better ? v : b.v;
+    b.key = better ? key : b.key;
 }
 
 // TIMING: each workgroup adds the clock cycles of its pivot steps' phases to
@@ -405,14 +409,14 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
                                                      uint64_t timeout, unsigned long long *__restrict__ tacc)
 {
     constexpr int RMAX = 16 * RM;
+    constexpr int NG = QG_T / 16;             // 16-lane groups
     __shared__ int piv[QR_MAXCOL];            // position -> column
-    __shared__ int posof[QR_MAXCOL];          // column -> position
     __shared__ double cd[W][RMAX];            // the W candidates' rows
-    __shared__ double svr[RMAX];              // the reflector's rows below t
+    __shared__ double rdiag[RMAX];            // R_tt of the steps taken
     __shared__ double cv[W];
     __shared__ int cp[W], cc[W];
-    __shared__ double rdv[QG_T / 64];
-    __shared__ int rdp[QG_T / 64], rdc[QG_T / 64];
+    __shared__ double rdv[NG];
+    __shared__ int32_t rdk[NG];
     __shared__ int s_fail;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int grp = tid >> 4, l16 = tid & 15;
@@ -435,17 +439,16 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
         const int a = it.y;
         const int rows = I.T_cnt[a], cols = I.ncols[a];
         double *G = Gall + (int64_t)q * ncol_max * ell;
-        for (int c = tid; c < cols; c += QG_T) {
-            piv[c] = c;
-            posof[c] = c;
-        }
+        for (int c = tid; c < cols; c += QG_T) piv[c] = c;
         double x[CPG][RM];
         double nv[CPG];
+        int32_t pj[CPG];                      // the column's position
         bool act[CPG];
 #pragma unroll
         for (int j = 0; j < CPG; ++j) {
-            const int c = w + W * (grp + 32 * j);
+            const int c = w + W * (grp + NG * j);
             act[j] = c < cols;
+            pj[j] = c;
             double sq = 0.0;
 #pragma unroll
             for (int r = 0; r < RM; ++r) {
@@ -460,48 +463,51 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
         const int kcap = min(smax, min(rows, cols));
         int k = kcap;
         double nrm0 = 0.0;
+        int lpc = -1, lpp = 0, lct = 0, lt = 0;   // the last swap: column, its position, the column it replaced, step
         for (int t = 0; t < kcap; ++t) {
             unsigned long long c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, c5 = 0;
             if constexpr (TIMING) c0 = clock64();
             // this workgroup's best active column
-            double bv = -1.0;
-            int bp = 0x7fffffff, bc = -1;
+            QrBest best{-1.0, 0x7fffffff};
 #pragma unroll
-            for (int j = 0; j < CPG; ++j) {
-                if (!act[j]) continue;
-                const int c = w + W * (grp + 32 * j);
-                const int pc = posof[c];
-                if (qg_better(nv[j], pc, bv, bp)) { bv = nv[j]; bp = pc; bc = c; }
+            for (int j = 0; j < CPG; ++j)
+                if (act[j]) qr_take(best, nv[j], pj[j] << 16 | (w + W * (grp + NG * j)));
+            if (l16 == 0) {
+                rdv[grp] = best.v;
+                rdk[grp] = best.key;
             }
-#pragma unroll
-            for (int o = 32; o >= 16; o >>= 1) {
-                const double ov = __shfl_xor(bv, o);
-                const int op = __shfl_xor(bp, o), oc = __shfl_xor(bc, o);
-                if (qg_better(ov, op, bv, bp)) { bv = ov; bp = op; bc = oc; }
-            }
-            if (lane == 0) { rdv[wv] = bv; rdp[wv] = bp; rdc[wv] = bc; }
             __syncthreads();
+            // the previous step's swap (every thread has read that step's piv)
+            if (tid == 0 && t > 0) {
+                piv[t - 1] = lpc;
+                piv[lpp] = lct;
+            }
             if constexpr (TIMING) c1 = clock64();
             ++gs;
             const int par = gs & 1;
             GangSlot *sl = slots + ((int64_t)gang * 2 + par) * W;
             double *sd = sdata + ((int64_t)gang * 2 + par) * W * RMAX;   // RMAX rows per member
-            // every thread reduces the waves' candidates (same order, same
-            // result), so no barrier is needed before the rows are published
-            bv = rdv[0];
-            bp = rdp[0];
-            bc = rdc[0];
-            for (int u = 1; u < QG_T / 64; ++u)
-                if (qg_better(rdv[u], rdp[u], bv, bp)) { bv = rdv[u]; bp = rdp[u]; bc = rdc[u]; }
+            // every row of 16 lanes reduces the groups' candidates (same result
+            // everywhere), so no barrier is needed before the rows are published
+            best.v = rdv[l16];
+            best.key = rdk[l16];
+            qr_take(best, rdv[16 + l16], rdk[16 + l16]);
+            qr_take(best, xor_lane<8>(best.v), row_move<8>(best.key));
+            qr_take(best, xor_lane<4>(best.v), row_move<4>(best.key));
+            qr_take(best, xor_lane<2>(best.v), row_move<2>(best.key));
+            qr_take(best, xor_lane<1>(best.v), row_move<1>(best.key));
+            const double bv = best.v;
+            const int bkey = __builtin_amdgcn_readfirstlane(best.key);
+            const int bp = bkey >> 16, bc = best.v >= 0.0 ? bkey & 0xffff : -1;
             if (tid == 0) {
                 __hip_atomic_store(&sl[w].v, bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&sl[w].pos, bp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&sl[w].col, bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             {
-                const int lbc = bc;
-                if (lbc >= 0 && grp == (lbc / W) % 32) {
-                    const int jb = (lbc / W) / 32;
+                const int lbc = __builtin_amdgcn_readfirstlane(bc);
+                if (lbc >= 0 && grp == (lbc / W) % NG) {
+                    const int jb = (lbc / W) / NG;
                     double *dst = sd + (int64_t)w * RMAX;
                     // whole slices from the one holding row t (a uniform test;
                     // rows < t and >= rows are written too and never read)
@@ -569,7 +575,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
             int gp = 0x7fffffff, pc = -1, pw = 0;
 #pragma unroll
             for (int u = 0; u < W; ++u)
-                if (cc[u] >= 0 && qg_better(cv[u], cp[u], gv, gp)) { gv = cv[u]; gp = cp[u]; pc = cc[u]; pw = u; }
+                if (cc[u] >= 0 && (cv[u] > gv || (cv[u] == gv && cp[u] < gp))) { gv = cv[u]; gp = cp[u]; pc = cc[u]; pw = u; }
             if (pc < 0) { k = t; break; }              // no active column with a finite norm
             const double nrm = sqrt(gv);
             if (t == 0) {
@@ -579,83 +585,66 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
                 k = t;
                 break;
             }
-            // swap positions t and posof[pc] (read again only after the
-            // barrier that follows the reflector rows below)
-            if (tid == 0) {
-                const int ct = piv[t], pp = posof[pc];
-                piv[t] = pc;
-                piv[pp] = ct;
-                posof[ct] = pp;
-                posof[pc] = t;
-            }
-            // the reflector, computed alike in every workgroup
-            const double *vs = cd[pw];
-            const double x0 = vs[t];
-            const double rtt = x0 >= 0.0 ? -nrm : nrm;
-            const double denom = x0 - rtt;
-            const double beta = (rtt - x0) / rtt;
-            const int rt = t / 16, lt = t % 16;
-            if (pw == w && grp == (pc / W) % 32) {
-                const int jp = (pc / W) / 32;
+            // positions t and gp are swapped (piv itself after the next barrier)
+            const int ct = piv[t];
+            lpc = pc;
+            lpp = gp;
+            lct = ct;
+            lt = t;
 #pragma unroll
-                for (int j = 0; j < CPG; ++j) {
-                    if (j != jp) continue;
-#pragma unroll
-                    for (int r = 0; r < RM; ++r) {
-                        if (r > rt) {
-                            x[j][r] = 0.0;             // rows past `rows` hold zeros already
-                        } else if (r == rt) {
-                            if (l16 > lt) x[j][r] = 0.0;
-                            else if (l16 == lt) x[j][r] = rtt;
-                        }
-                    }
+            for (int j = 0; j < CPG; ++j) {
+                const int c = w + W * (grp + NG * j);
+                if (c == ct) pj[j] = gp;
+                if (c == pc) {
+                    pj[j] = t;
                     act[j] = false;
                 }
             }
-            for (int i = tid; i < RMAX; i += QG_T) svr[i] = (i > t && i < rows) ? vs[i] / denom : 0.0;
-            __syncthreads();
-            double vr[RM];
+            // the reflector H = I - c u u^T (u_t = x_t - R_tt, the column's rows
+            // below t as they are, c = -1 / (R_tt u_t)), alike in every workgroup
+            const double *vs = cd[pw];
+            const double x0 = vs[t];
+            const double rtt = x0 >= 0.0 ? -nrm : nrm, ut = x0 - rtt;
+            const double cu = -1.0 / (rtt * ut);
+            if (tid == 0) rdiag[t] = rtt;
+            const int rt = t / 16, tl = t - l16;       // row l16 + 16 r is below t where 16 r > tl
+            double u[RM];
 #pragma unroll
-            for (int r = 0; r < RM; ++r) vr[r] = svr[l16 + 16 * r];
+            for (int r = 0; r < RM; ++r) {
+                const double z = vs[l16 + 16 * r];
+                u[r] = 16 * r < rows - l16 ? (16 * r > tl ? z : 16 * r == tl ? ut : 0.0) : 0.0;
+            }
             if constexpr (TIMING) c5 = clock64();
-            const int src = (lane & ~15) | lt;
-            const bool lane_after = l16 > lt, lane_at = l16 == lt;
+            // JB columns at a time; slices above rt hold rows of R (uniform skip)
+            constexpr int JB = 2;
 #pragma unroll
-            for (int j = 0; j < CPG; ++j) {
-                if (!act[j]) continue;                 // group-uniform
-                // vr is zero outside rows (t, rows): the dot product needs no
-                // row test
-                double sdot = 0.0, top = 0.0;
+            for (int j0 = 0; j0 < CPG; j0 += JB) {
+                double sd[JB], ns[JB];
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] = ns[j] = 0.0;
 #pragma unroll
                 for (int r = 0; r < RM; ++r) {
-                    sdot += vr[r] * x[j][r];
-                    if (r == rt) top = x[j][r];
+                    if (r < rt) continue;
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) sd[j] += u[r] * x[j0 + j][r];
                 }
-                sdot = group16_sum(sdot);
-                top = __shfl(top, src);
-                const double f = beta * (sdot + top);
-                double ns = 0.0;
-                // slices after rt change whole (their rows past `rows` hold
-                // zeros with zero reflector entries and stay zero), slice rt
-                // changes its rows > t and row t becomes R(t, c), slices
-                // before it keep their R rows: uniform tests per slice and
-                // one lane test, instead of a row test per element
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] = group16_sum(sd[j]);
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? cu * sd[j] : 0.0;   // pivoted: rows kept
 #pragma unroll
                 for (int r = 0; r < RM; ++r) {
-                    const double y = x[j][r] - f * vr[r];
-                    if (r > rt) {
-                        x[j][r] = y;
-                        ns += y * y;
-                    } else if (r == rt) {
-                        if (lane_after) {
-                            x[j][r] = y;
-                            ns += y * y;
-                        } else if (lane_at) {
-                            x[j][r] = top - f;
-                        }
+                    if (r < rt) continue;
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) {
+                        const double y = x[j0 + j][r] - sd[j] * u[r];
+                        x[j0 + j][r] = y;
+                        if (r > rt) ns[j] += y * y;
+                        else ns[j] += 16 * r > tl ? y * y : 0.0;
                     }
                 }
-                nv[j] = group16_sum(ns);
+#pragma unroll
+                for (int j = 0; j < JB; ++j) nv[j0 + j] = group16_sum(ns[j]);
             }
             if constexpr (TIMING) {
                 const unsigned long long c6 = clock64();
@@ -668,18 +657,25 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
                 tph[6] += 1;
             }
         }
-        // every column to its final position
+        // the last step's swap, and every column to its final position (a
+        // pivot's rows end at its position)
+        if (tid == 0 && lpc >= 0) {
+            piv[lt] = lpc;
+            piv[lpp] = lct;
+        }
         __syncthreads();
+        int rl = rows - l16;
+        asm volatile("" : "+v"(rl));          // (nothing of this is computed ahead of the steps)
 #pragma unroll
         for (int j = 0; j < CPG; ++j) {
-            const int c = w + W * (grp + 32 * j);
+            const int c = w + W * (grp + NG * j);
             if (c < cols) {
-                const int pos = posof[c];
+                double *gc = G + (int64_t)pj[j] * ell + l16;
+                const int tl = act[j] ? RMAX : pj[j] - l16;
+                const double d = act[j] ? 0.0 : rdiag[pj[j]];
 #pragma unroll
-                for (int r = 0; r < RM; ++r) {
-                    const int i = l16 + 16 * r;
-                    if (i < rows) G[(int64_t)pos * ell + i] = x[j][r];
-                }
+                for (int r = 0; r < RM; ++r)
+                    if (16 * r < rl) gc[16 * r] = 16 * r < tl ? x[j][r] : 16 * r == tl ? d : 0.0;
             }
         }
         if (w == 0) {
@@ -691,6 +687,196 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
         if (tid == 0)
             for (int i = 0; i < 7; ++i) atomicAdd(&tacc[i], tph[i]);
     }
+}
+
+// ---------------------------------------------------------------- QRCP in registers
+// The factorization of a node whose columns fit one workgroup's registers
+// (cols <= T / 16 CPG, rows <= 16 RM): 16-lane group g keeps columns g + T / 16 j
+// in slot j, lane l16 rows l16 + 16 r, so G is read and written once and a pivot
+// step exchanges only the best column through LDS, with two barriers.  The pivot
+// rule, the swaps and the rank rule are k_qrcp's; the reflector H = I - c u u^T
+// is applied unscaled (u_t = G_tt - R_tt, u_i = G_it, c = -1 / (R_tt u_t)): one
+// quotient per step, and row t is an entry like the others.  Sums across lanes
+// are DPP steps (no LDS round trip).  Bound by the latency of a step's chain
+// (argmax, square root, quotient, two barriers, two sums over the lanes)
+// and the FP64 updates (3 FMA per held entry and step; slices above row t are
+// skipped).  100,000 points, m = 256, s = 128, l = 148: 15.4 ms with k_qrcp,
+// which streams G from memory every step, 6.2 ms here.
+constexpr int QR_PAD = 160;                  // 16 RM at most
+
+template <int T, int RM, int CPG, int JB>
+__global__ __launch_bounds__(T) void k_qrcp_reg(double *__restrict__ Gall, int ell, int ncol_max,
+                                                const SkelInst *__restrict__ inst,
+                                                const int2 *__restrict__ items, int smax, double tau)
+{
+    constexpr int NG = T / 16;                // groups: rows of 16 lanes
+    static_assert(NG == 16 || NG == 32 || NG == 64, "every lane of a row takes NG / 16 of the groups' best");
+    static_assert(16 * RM <= QR_PAD && CPG % JB == 0, "padding of G, whole blocks of columns");
+    __shared__ double buf[16 * RM];           // the pivot column
+    __shared__ double rdiag[16 * RM];         // R_tt of the steps taken
+    __shared__ double rdv[NG];
+    __shared__ int32_t rdk[NG];
+    __shared__ int32_t piv[NG * CPG];         // position -> column
+    const int tid = threadIdx.x, grp = tid >> 4, l16 = tid & 15;
+    const int q = blockIdx.x;
+    const int2 it = items[q];
+    const SkelInst &I = inst[it.x];
+    const int a = it.y;
+    const int rows = I.T_cnt[a], cols = I.ncols[a];
+    if (rows <= 0 || cols <= 0) {             // uniform: rank 0
+        for (int c = tid; c < cols; c += T) I.colperm[(int64_t)a * I.ncol_max + c] = c;
+        if (tid == 0) I.skk[a] = 0;
+        return;
+    }
+    double *G = Gall + (int64_t)q * ncol_max * ell;
+    for (int c = tid; c < cols; c += T) piv[c] = c;
+    double x[CPG][RM], nv[CPG];
+    int32_t pj[CPG];                          // the column's position
+    bool act[CPG];
+    // unconditional loads at fixed offsets, a column's in flight together: past
+    // its rows they read the next columns (G is allocated with QR_PAD more)
+#pragma unroll
+    for (int j = 0; j < CPG; ++j) {
+        const int c = grp + NG * j;
+        const double *gc = G + (int64_t)min(c, cols - 1) * ell + l16;
+        act[j] = c < cols;
+        pj[j] = c;
+        nv[j] = 0.0;
+#pragma unroll
+        for (int r = 0; r < RM; ++r) x[j][r] = gc[16 * r];
+#pragma unroll
+        for (int r = 0; r < RM; ++r) {
+            asm volatile("" : "+v"(x[j][r]));              // (not sunk into branches)
+            x[j][r] = (act[j] && 16 * r < rows - l16) ? x[j][r] : 0.0;
+            nv[j] += x[j][r] * x[j][r];
+        }
+        nv[j] = group16_sum(nv[j]);
+    }
+    const double teff = tau > TAU_FLOOR ? tau : TAU_FLOOR;
+    const int kcap = min(smax, min(rows, cols));
+    int k = kcap;
+    double nrm0 = 0.0;
+    for (int t = 0; t < kcap; ++t) {
+        const int rt = t >> 4;
+        // the largest residual norm, ties to the lowest position
+        QrBest b{-1.0, 0x7fffffff};
+#pragma unroll
+        for (int j = 0; j < CPG; ++j)
+            if (act[j]) qr_take(b, nv[j], pj[j] << 16 | (grp + NG * j));
+        if (l16 == 0) {
+            rdv[grp] = b.v;
+            rdk[grp] = b.key;
+        }
+        __syncthreads();
+        b.v = rdv[l16];
+        b.key = rdk[l16];
+#pragma unroll
+        for (int i = 1; i < NG / 16; ++i) qr_take(b, rdv[16 * i + l16], rdk[16 * i + l16]);
+        qr_take(b, xor_lane<8>(b.v), row_move<8>(b.key));
+        qr_take(b, xor_lane<4>(b.v), row_move<4>(b.key));
+        qr_take(b, xor_lane<2>(b.v), row_move<2>(b.key));
+        qr_take(b, xor_lane<1>(b.v), row_move<1>(b.key));
+        if (!(b.v >= 0.0)) { k = t; break; }       // no active column with a finite norm
+        const double nrm = sqrt(b.v);
+        if (t == 0) {
+            nrm0 = nrm;
+            if (!(nrm0 > 0.0)) { k = 0; break; }
+        } else if (nrm <= teff * nrm0) {
+            k = t;
+            break;
+        }
+        const int key = __builtin_amdgcn_readfirstlane(b.key);     // the same in every lane
+        const int pp = key >> 16, pc = key & 0xffff, ct = piv[t], jp = pc / NG;
+        if (grp == pc % NG) {
+            // publish the column (its rows below t become zeros, row t R_tt,
+            // when it is written out)
+#pragma unroll
+            for (int j = 0; j < CPG; ++j) {
+                if (j != jp) continue;
+                // (keep the branches apart: merged ones would index x and move
+                // it to memory)
+                asm volatile("; slot %0" ::"i"(j));
+#pragma unroll
+                for (int r = 0; r < RM; ++r) buf[l16 + 16 * r] = x[j][r];
+                asm volatile("; slot %0 done" ::"i"(j));
+            }
+        }
+        // positions t and pp are swapped
+#pragma unroll
+        for (int j = 0; j < CPG; ++j) {
+            const int c = grp + NG * j;
+            if (c == ct) pj[j] = pp;
+            if (c == pc) {
+                pj[j] = t;
+                act[j] = false;
+            }
+        }
+        __syncthreads();
+        const double x0 = buf[t];
+        const double rtt = x0 >= 0.0 ? -nrm : nrm, ut = x0 - rtt;
+        if (tid == 0) {
+            piv[t] = pc;
+            piv[pp] = ct;
+            rdiag[t] = rtt;
+        }
+        const double c = -1.0 / (rtt * ut);
+        const int tl = t - l16;                    // row l16 + 16 r is below t where 16 r > tl
+        double u[RM];
+#pragma unroll
+        for (int r = 0; r < RM; ++r) {
+            const double z = buf[l16 + 16 * r];
+            u[r] = 16 * r > tl ? z : 16 * r == tl ? ut : 0.0;
+        }
+        // JB columns at a time
+#pragma unroll
+        for (int j0 = 0; j0 < CPG; j0 += JB) {
+            double sd[JB], ns[JB];
+#pragma unroll
+            for (int j = 0; j < JB; ++j) sd[j] = ns[j] = 0.0;
+#pragma unroll
+            for (int r = 0; r < RM; ++r) {
+                if (r < rt) continue;              // uniform: those slices hold R rows
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] += u[r] * x[j0 + j][r];
+            }
+#pragma unroll
+            for (int j = 0; j < JB; ++j) sd[j] = group16_sum(sd[j]);
+#pragma unroll
+            for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? c * sd[j] : 0.0;    // pivoted: rows kept
+#pragma unroll
+            for (int r = 0; r < RM; ++r) {
+                if (r < rt) continue;
+#pragma unroll
+                for (int j = 0; j < JB; ++j) {
+                    const double y = x[j0 + j][r] - sd[j] * u[r];
+                    x[j0 + j][r] = y;
+                    if (r > rt) ns[j] += y * y;
+                    else ns[j] += 16 * r > tl ? y * y : 0.0;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < JB; ++j) nv[j0 + j] = group16_sum(ns[j]);
+        }
+    }
+    // every column to its final position
+    __syncthreads();                          // rdiag
+    int rl = rows - l16;
+    asm volatile("" : "+v"(rl));              // (nothing of this is computed ahead of the steps)
+#pragma unroll
+    for (int j = 0; j < CPG; ++j) {
+        const int c = grp + NG * j;
+        if (c < cols) {
+            double *gc = G + (int64_t)pj[j] * ell + l16;
+            // a pivot's rows end at its position
+            const int tl = act[j] ? 16 * RM : pj[j] - l16;
+            const double d = act[j] ? 0.0 : rdiag[pj[j]];
+#pragma unroll
+            for (int r = 0; r < RM; ++r)
+                if (16 * r < rl) gc[16 * r] = 16 * r < tl ? x[j][r] : 16 * r == tl ? d : 0.0;
+        }
+    }
+    for (int c = tid; c < cols; c += T) I.colperm[(int64_t)a * I.ncol_max + c] = piv[c];
+    if (tid == 0) I.skk[a] = k;
 }
 
 // P = R11^{-1} R12 in place over R12 (FP64).  Block per (node, chunk of SV_C
@@ -1025,7 +1211,7 @@ void skeletonize_multi(const std::vector<askit_handle *> &hs, hipStream_t s)
     }
     const size_t per = (size_t)ncm * ell * sizeof(double);
     const int batch = (int)std::max<size_t>(1, std::min<size_t>((size_t)maxlev, (size_t)(4ull << 30) / per));
-    double *G = (double *)ta(per * batch);
+    double *G = (double *)ta(per * batch + sizeof(double) * QR_PAD);
     int32_t *colpos = (int32_t *)ta(sizeof(int32_t) * (size_t)ncm * batch);
     const size_t sv_lds = sizeof(double) * (size_t)std::min(smax, ell) * SV_C;
     if (sv_lds > 64 * 1024)
@@ -1040,13 +1226,21 @@ void skeletonize_multi(const std::vector<askit_handle *> &hs, hipStream_t s)
         HIPC(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
         HIPC(hipDeviceGetAttribute(&clk_khz, hipDeviceAttributeWallClockRate, dev));
     }
-    // (by default the nodes of large point sets only, as each handle alone
-    // would: a node takes the same form of the QR alone and fused).
-    // ASKIT_QR_GANG=1 uses it at any size, 0 never.
+    // The form of the QR follows from the parameters alone (which the handles
+    // share), so that a node takes the same one alone and fused: a register
+    // form wherever a node's bounds fit one (0.41 against 0.75 ms of streaming
+    // at 4096 points with m = 128, s = 64; 6.2 against 15.4 ms at 100,000 with
+    // m = 256, s = 128), else the gang where they fit it (the whole setup at m =
+    // 512, s = 256, d = 64: 7.8 against 11.9 ms at 2500 points, 28 against 38 at
+    // 100,000), else streaming.  ASKIT_QR_GANG=1 prefers the gang, 0 never
+    // takes it.
     const char *genv = std::getenv("ASKIT_QR_GANG");
     const int gmode = genv ? std::atoi(genv) : -1;
-    const bool can_gang = coop && clk_khz > 0 && ncm <= 512 && ell <= 16 * 18 && gmode != 0;
-    auto gang_node = [&](const askit_handle *h) { return can_gang && (gmode == 1 || h->N >= (1 << 18)); };
+    const int rcols = std::max(h0->m, 2 * smax);
+    const bool fits_reg = (ell <= 16 * 4 && rcols <= 64) || (ell <= 16 * 6 && rcols <= 128) ||
+                          (ell <= 16 * 10 && rcols <= 256);
+    const bool can_gang = coop && clk_khz > 0 && rcols <= 512 && ell <= 16 * 18 && gmode != 0;
+    auto gang_node = [&](const askit_handle *) { return can_gang && (gmode == 1 || !fits_reg); };
     bool use_gang = false;
     for (auto *h : hs) use_gang = use_gang || gang_node(h);
     const uint64_t g_timeout = (uint64_t)((double)clk_khz * 1000.0 * QG_TIMEOUT_S);
@@ -1140,6 +1334,15 @@ void skeletonize_multi(const std::vector<askit_handle *> &hs, hipStream_t s)
         double *Gr = G + (int64_t)q0i * ncm * ell;
         const int2 *ir = d_items + q0i;
         if (nrest == 0) {
+        } else if (ell <= 16 * 4 && rcols <= 64) {
+            hipLaunchKernelGGL((k_qrcp_reg<256, 4, 4, 4>), dim3((unsigned)nrest), dim3(256), 0, s, Gr, ell, ncm, d_inst,
+                               ir, smax, tau);
+        } else if (ell <= 16 * 6 && rcols <= 128) {
+            hipLaunchKernelGGL((k_qrcp_reg<512, 6, 4, 4>), dim3((unsigned)nrest), dim3(512), 0, s, Gr, ell, ncm, d_inst,
+                               ir, smax, tau);
+        } else if (ell <= 16 * 10 && rcols <= 256) {
+            hipLaunchKernelGGL((k_qrcp_reg<512, 10, 8, 8>), dim3((unsigned)nrest), dim3(512), 0, s, Gr, ell, ncm,
+                               d_inst, ir, smax, tau);
         } else if (ell <= 16 * 8)
             hipLaunchKernelGGL((k_qrcp<512, 8>), dim3((unsigned)nrest), dim3(512), 0, s, Gr, ell, ncm, d_inst,
                                ir, smax, tau, nrest);
