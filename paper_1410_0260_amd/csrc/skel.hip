@@ -379,9 +379,9 @@ constexpr int QG_T = 512;
 constexpr double QG_TIMEOUT_S = 10.0;                // wait limit
 
 struct GangSlot {
-    double v;
-    int32_t pos, col;
-    int32_t seq, pad;
+    double v;                                 // largest residual norm (squared), -1: no active column
+    int32_t key;                              // its position << 16 | column
+    int32_t seq;
 };
 
 struct QrBest {
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
     __shared__ double cd[W][RMAX];            // the W candidates' rows
     __shared__ double rdiag[RMAX];            // R_tt of the steps taken
     __shared__ double cv[W];
-    __shared__ int cp[W], cc[W];
+    __shared__ int32_t ck[W];
     __shared__ double rdv[NG];
     __shared__ int32_t rdk[NG];
     __shared__ int s_fail;
@@ -440,6 +440,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
         const int rows = I.T_cnt[a], cols = I.ncols[a];
         double *G = Gall + (int64_t)q * ncol_max * ell;
         for (int c = tid; c < cols; c += QG_T) piv[c] = c;
+        for (int e = tid; e < W * RMAX; e += QG_T) (&cd[0][0])[e] = 0.0;      // rows past `rows` stay zero
         double x[CPG][RM];
         double nv[CPG];
         int32_t pj[CPG];                      // the column's position
@@ -496,17 +497,14 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
             qr_take(best, xor_lane<4>(best.v), row_move<4>(best.key));
             qr_take(best, xor_lane<2>(best.v), row_move<2>(best.key));
             qr_take(best, xor_lane<1>(best.v), row_move<1>(best.key));
-            const double bv = best.v;
             const int bkey = __builtin_amdgcn_readfirstlane(best.key);
-            const int bp = bkey >> 16, bc = best.v >= 0.0 ? bkey & 0xffff : -1;
             if (tid == 0) {
-                __hip_atomic_store(&sl[w].v, bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&sl[w].pos, bp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&sl[w].col, bc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&sl[w].v, best.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&sl[w].key, best.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             {
-                const int lbc = __builtin_amdgcn_readfirstlane(bc);
-                if (lbc >= 0 && grp == (lbc / W) % NG) {
+                const int lbc = bkey & 0xffff;
+                if (bkey != 0x7fffffff && grp == (lbc / W) % NG) {
                     const int jb = (lbc / W) / NG;
                     double *dst = sd + (int64_t)w * RMAX;
                     // whole slices from the one holding row t (a uniform test;
@@ -561,8 +559,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
             // (a workgroup without a candidate left stale rows: not used)
             if (tid < W) {
                 cv[tid] = __hip_atomic_load(&sl[tid].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                cp[tid] = __hip_atomic_load(&sl[tid].pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                cc[tid] = __hip_atomic_load(&sl[tid].col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ck[tid] = __hip_atomic_load(&sl[tid].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             for (int e = tid; e < W * (rows - t); e += QG_T) {
                 const int u = e / (rows - t), i = t + e % (rows - t);
@@ -571,12 +568,16 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
             __syncthreads();
             if (s_fail) return;
             if constexpr (TIMING) c4 = clock64();
-            double gv = -1.0;
-            int gp = 0x7fffffff, pc = -1, pw = 0;
-#pragma unroll
-            for (int u = 0; u < W; ++u)
-                if (cc[u] >= 0 && (cv[u] > gv || (cv[u] == gv && cp[u] < gp))) { gv = cv[u]; gp = cp[u]; pc = cc[u]; pw = u; }
-            if (pc < 0) { k = t; break; }              // no active column with a finite norm
+            // the best of the W candidates (every row of 16 lanes alike)
+            best.v = cv[l16 & (W - 1)];
+            best.key = ck[l16 & (W - 1)];
+            if constexpr (W > 4) qr_take(best, xor_lane<4>(best.v), row_move<4>(best.key));
+            qr_take(best, xor_lane<2>(best.v), row_move<2>(best.key));
+            qr_take(best, xor_lane<1>(best.v), row_move<1>(best.key));
+            const double gv = best.v;
+            if (!(gv >= 0.0)) { k = t; break; }        // no active column with a finite norm
+            const int gkey = __builtin_amdgcn_readfirstlane(best.key);
+            const int gp = gkey >> 16, pc = gkey & 0xffff, pw = pc % W;   // column c belongs to workgroup c % W
             const double nrm = sqrt(gv);
             if (t == 0) {
                 nrm0 = nrm;
@@ -612,11 +613,11 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
 #pragma unroll
             for (int r = 0; r < RM; ++r) {
                 const double z = vs[l16 + 16 * r];
-                u[r] = 16 * r < rows - l16 ? (16 * r > tl ? z : 16 * r == tl ? ut : 0.0) : 0.0;
+                u[r] = 16 * r > tl ? z : 16 * r == tl ? ut : 0.0;
             }
             if constexpr (TIMING) c5 = clock64();
             // JB columns at a time; slices above rt hold rows of R (uniform skip)
-            constexpr int JB = 2;
+            constexpr int JB = CPG < 4 ? CPG : 4;
 #pragma unroll
             for (int j0 = 0; j0 < CPG; j0 += JB) {
                 double sd[JB], ns[JB];
@@ -1074,7 +1075,6 @@ __global__ void k_gang_reset(GangSlot *__restrict__ slots, int n, int32_t *__res
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
         slots[i].seq = 0;
-        slots[i].col = -1;
     }
     if (i == 0 && err) *err = 0;
 }
