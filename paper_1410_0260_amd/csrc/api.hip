@@ -611,8 +611,9 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
         // the search sweeps the points in a finer order than the tree's (leaves
         // split on into cells of at most 64 points): compact tiles, so far
         // (row block, tile) pairs are skipped; results are ids and exact
-        // distances, independent of the order
-        const bool fine = h->depth > 0 && N > 64 * 64 && !std::getenv("ASKIT_KNN_TREE_ORDER");
+        // distances, independent of the order.  Small point sets are swept
+        // whole (knn_candidates), so the order gains nothing there
+        const bool fine = h->depth > 0 && N > KNN_SMALL_N && !std::getenv("ASKIT_KNN_TREE_ORDER");
         int32_t *perm_f = h->perm;
         float *Xt_f = h->Xt, *Xn_f = h->Xn;
         uint16_t *Xh_f = h->Xh, *Xl_f = h->Xl;
@@ -628,9 +629,16 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
         }
         HIPC(hipEventRecord(k0, s));
         float fms = 0.f;
-        knn_candidates(Xh_f, Xl_f, Xn_f, N, Xh_f, Xl_f, Xn_f, N, dp, true, true, cand, thr,
-                       bad + 1, bad, s, &fms, &h->knn_filter_launches, &h->knn_retry_rows, &h->ksamp,
-                       &h->knn_retry_list, Xt_f, d, &h->knn_tiles_swept, knn_nsel(kappa));
+        const bool direct = kappa > KNN_DIRECT && dp <= 128;
+        if (direct) {
+            knn_direct(Xt_f, Xh_f, Xl_f, Xn_f, N, d, dp, kappa, mx, perm_f, h->knn_idx, h->knn_d, s, &fms,
+                       &h->knn_filter_launches, &h->knn_retry_list, &h->knn_tiles_swept);
+            h->knn_retry_rows = (int)h->knn_retry_list.size();
+        } else {
+            knn_candidates(Xh_f, Xl_f, Xn_f, N, Xh_f, Xl_f, Xn_f, N, dp, true, true, cand, thr,
+                           bad + 1, bad, s, &fms, &h->knn_filter_launches, &h->knn_retry_rows, &h->ksamp,
+                           &h->knn_retry_list, Xt_f, d, &h->knn_tiles_swept, knn_nsel(kappa));
+        }
         h->t_knn_filter = fms;
         HIPC(hipEventRecord(k1, s));
         if (fine && !h->knn_retry_list.empty()) {
@@ -648,10 +656,12 @@ static void setup_impl(const float *X, int64_t N, int32_t d, int64_t ldx, const 
         }
         float *tb;
         HIPC(ws_alloc((void **)&tb, sizeof(float) * N, s));
-        knn_refine(Xt_f, N, Xt_f, N, d, dp, kappa, cand, thr, Xn_f, mx, perm_f, perm_f,
-                   h->knn_idx, h->knn_d, bad + 1, bad, tb, s);
         int32_t nbad = 0;
-        HIPC(hipMemcpyAsync(&nbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        if (!direct) {
+            knn_refine(Xt_f, N, Xt_f, N, d, dp, kappa, cand, thr, Xn_f, mx, perm_f, perm_f, h->knn_idx, h->knn_d,
+                       bad + 1, bad, tb, s);
+            HIPC(hipMemcpyAsync(&nbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        }
         HIPC(hipStreamSynchronize(s));
         h->knn_uncertified = nbad;
         float kms = 0.f;

@@ -305,6 +305,16 @@ void knn_fallback(const float *Q, const uint16_t *Qh, const uint16_t *Ql, const 
                   const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int d, int dp, int kappa,
                   bool exclude_self, const int32_t *rows, int nrows, const float *tbound, const int32_t *idmap,
                   const int32_t *rowmap, int32_t *idx, double *dist, hipStream_t s);
+// The kappa nearest neighbours of every point of a set among the others (rows in
+// sweep order, idmap: their ids, which are also the output rows) for kappa
+// above KNN_DIRECT, where the candidates above leave the certificate no room.
+// dp <= 128; the counters as knn_candidates gives them.
+constexpr int KNN_DIRECT = 48;
+// Point sets up to this size are searched whole, in the tree's order.
+constexpr int64_t KNN_SMALL_N = 32768;
+void knn_direct(const float *Xf, const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int d, int dp,
+                int kappa, float maxnorm, const int32_t *idmap, int32_t *idx, double *dist, hipStream_t s,
+                float *t_filter_ms, int *n_filter, std::vector<int32_t> *retry_rows, int64_t *tiles_swept);
 void knn_exact_rows(const float *Q, const float *X, int64_t N, int d, int dp, int kappa,
                     bool exclude_self, const int32_t *rows, int nrows, const int32_t *idmap,
                     const int32_t *rowmap, int32_t *idx, double *dist, hipStream_t s);

@@ -17,6 +17,7 @@
 //   approximate distance as threshold; the list sweeps keep 64.
 //   3. k_knn_exact: full FP64 scan for the rows that are not certified.
 #include "askit_impl.h"
+#include "wave_list.h"
 
 #include <algorithm>
 #include <cstdlib>
@@ -1075,9 +1076,11 @@ static void list_sweep(hipStream_t s, const uint16_t *Qh, const uint16_t *Ql, co
 static int filter_segments(int64_t m, int64_t ntiles)
 {
     const int64_t rb = (m + KB_M - 1) / KB_M;
-    return (int)std::max<int64_t>(1, std::min<int64_t>({64, 2048 / rb, ntiles / 16}));
+    // at least 16 tiles each, 4 where few row blocks leave the chip idle
+    return (int)std::max<int64_t>(1, std::min<int64_t>({64, 2048 / rb, ntiles / (rb <= 64 ? 4 : 16)}));
 }
 
+constexpr int KNN_SMALL = KNN_SMALL_N / KB_N;   // tiles of a small point set
 constexpr int KNN_WIN = 64;                 // window tiles (4096 points)
 constexpr int KNN_CAP = 1024;               // filter output per row
 constexpr int64_t KNN_CHUNK = 1 << 20;      // query rows per filter pass (bounds the buffers)
@@ -1149,6 +1152,26 @@ static void sample_thresholds(int dp, hipStream_t s, const uint16_t *Qh, const u
                       nullptr, false, 0, nullptr);
         widen(thr, M, s);
     }
+}
+
+// Thresholds of the point set against itself: the nsel-th approximate
+// distance among the 4096 sweep-order neighbours of a row's block, in three
+// steps with the same arithmetic: the nsel-th of the 4 tiles around the block's
+// rows (its own two and one on each side; every point passes at +inf) bounds
+// it; the threshold filter over the window at that bound keeps every closer
+// point (so at least those nsel); their nsel-th is the exact window value (or a
+// bound, when more than the capacity survive).  A point set no larger than the
+// window keeps the first bound.  thr leaves widened; the candidate lists (in cand) are scratch.
+static void window_thresholds(int dp, hipStream_t s, const uint16_t *Qh, const uint16_t *Ql, const float *Qn,
+                              int64_t M, const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int ex,
+                              int64_t chunk, float *thr, const FilterBufs &B, int32_t *cand, bool small)
+{
+    hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, thr, M, INFINITY);
+    filter_select(dp, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, chunk, thr, B, cand, nullptr, false, 4, nullptr);
+    widen(thr, M, s);
+    if (small && N <= KNN_WIN * KB_N) return;
+    filter_select(dp, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, chunk, thr, B, cand, nullptr, false, KNN_WIN, nullptr);
+    widen(thr, M, s);
 }
 
 // Retry rows of the point set against itself (tree positions rows[0, n)),
@@ -1537,14 +1560,19 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     const bool have_samp = samp && samp->levels > 0 && ntiles > 4 * KNN_WIN;
     // new points against the set: thresholds from the strided samples
     const bool sampled = !exclude_self && !start_local && have_samp;
-    if (!sampled && (!start_local || ntiles <= 4 * KNN_WIN)) {
+    if (!sampled && !start_local) {
         KNN_DISPATCH(list_sweep, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, sl, (const int32_t *)nullptr, false, cand,
                      thr);
         return;
     }
+    // a small point set: the whole sweep is short, so it runs in column
+    // segments in the tree's order, without tile lists (whose order, lists and
+    // host waits cost more: 2.3 against 1.0 ms of search at 16,384 x 4).  4096 x
+    // 8: 3.2 ms with list sweeps, 0.28 this way
+    const bool small = start_local && ntiles <= KNN_SMALL;
     // the point set against itself with every row's segment in one buffer:
     // one triangular sweep (each unordered pair once); else row chunks
-    const bool sym = exclude_self && Qh == Xh && M == N && (double)N * KNN_CAP * 8.0 <= 48.0 * (1ull << 30);
+    const bool sym = !small && exclude_self && Qh == Xh && M == N && (double)N * KNN_CAP * 8.0 <= 48.0 * (1ull << 30);
     const int64_t chunk = sym ? M : KNN_CHUNK;
     const int64_t mc = std::min<int64_t>(M, chunk);
     FilterBufs B;
@@ -1559,19 +1587,7 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     if (sampled) {
         sample_thresholds(dp, s, Qh, Ql, Qn, M, *samp, chunk, thr, B, cand);
     } else {
-        // window threshold: thr = nsel-th approximate distance among the 4096
-        // tree-order neighbours of the row's block, in three steps with the
-        // same arithmetic: the nsel-th of the 4 tiles around the block's rows
-        // (its own two and one on each side; every point passes at +inf)
-        // bounds it; the threshold filter over the window at that bound keeps
-        // every closer point (so at least those nsel); their nsel-th is the
-        // exact window value (or a bound, when more than the capacity survive)
-        hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, thr, M, INFINITY);
-        filter_select(dp, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, chunk, thr, B, cand, nullptr, false, 4, nullptr);
-        widen(thr, M, s);
-        filter_select(dp, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, chunk, thr, B, cand, nullptr, false, KNN_WIN,
-                      nullptr);
-        widen(thr, M, s);
+        window_thresholds(dp, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, chunk, thr, B, cand, small);
     }
     // symmetric sweep: only the (row block, tile) pairs whose bounding balls
     // come within the thresholds
@@ -1615,10 +1631,10 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     // 64th distance)
     const int32_t *list = retry + 1;
     int32_t nlist = nretry;
-    if (nretry > 0 && nretry <= mc && exclude_self && have_samp && Qh == Xh) {
-        // the point set against itself: the sampled thresholds on compact
-        // copies of the rows, then the filter over all points (one pass: the
-        // rows fit the filter buffers)
+    if (nretry > 0 && nretry <= mc && exclude_self && Qh == Xh) {
+        // the point set against itself: the sampled thresholds (large sets) on
+        // compact copies of the rows, then the filter over all points (one
+        // pass: the rows fit the filter buffers)
         const int64_t n = nretry;
         uint16_t *Bh, *Bl;
         float *Bn, *tc;
@@ -1642,7 +1658,7 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
                            Bn, tc);
         // seeded with the bound the selection left (the nsel-th of the
         // row's stored survivors, real points, widened)
-        sample_thresholds(dp, s, Bh, Bl, Bn, n, *samp, n, tc, B, cc, true);
+        if (have_samp) sample_thresholds(dp, s, Bh, Bl, Bn, n, *samp, n, tc, B, cc, true);
         // the filter over every point, only on the tiles the rows' sampled
         // thresholds can reach (the same survivors as the full sweep)
         std::vector<void *> rtmp;
@@ -1860,69 +1876,54 @@ void knn_refine(const float *Q, int64_t M, const float *X, int64_t N, int d, int
 }
 
 // ---------------------------------------------------------------- exact fallback
-// One block per row: every thread keeps a sorted top-kappa of a strided slice
-// of the points, then the lists are merged pairwise.
-constexpr int KX_T = 128;
-constexpr int KX_K = 64;     // largest kappa supported by the fallback
+// One wave per (row, segment of the points): the segment's 64 nearest by
+// canonical FP64 distances, kept sorted across the lanes; then one wave per row
+// merges its segments' lists.  The rows are few, so the points are split: one
+// workgroup per row with a list per thread took 3.3 ms for a handful of rows
+// against 100,000 points.
+constexpr int KX_SEG = 4096;      // points per segment, at least
 
-__global__ __launch_bounds__(KX_T) void k_knn_exact(const float *__restrict__ Qb,
-                                                    const float *__restrict__ X, int64_t N, int d,
-                                                    int dp, int kappa, int excl,
-                                                    const int32_t *__restrict__ rows,
-                                                    const int32_t *__restrict__ idmap,
-                                                    const int32_t *__restrict__ rowmap,
-                                                    int32_t *__restrict__ idx,
-                                                    double *__restrict__ dist)
+__global__ __launch_bounds__(64) void k_knn_exact(const float *__restrict__ Qb, const float *__restrict__ X,
+                                                  int64_t N, int d, int dp, int kappa, int excl,
+                                                  const int32_t *__restrict__ rows, int64_t seg,
+                                                  const int32_t *__restrict__ idmap, double *__restrict__ pd,
+                                                  int32_t *__restrict__ pi)
 {
-    extern __shared__ unsigned char smem[];
-    double *ld = reinterpret_cast<double *>(smem);
-    int *li = reinterpret_cast<int *>(ld + KX_T * kappa);
-    int tid = threadIdx.x;
-    int64_t row = rows[blockIdx.x];
+    const int lane = threadIdx.x;
+    const int64_t row = rows[blockIdx.y];
     const float *q = Qb + row * dp;
-    double *md = ld + tid * kappa;
-    int *mi = li + tid * kappa;
-    for (int t = 0; t < kappa; ++t) {
-        md[t] = INFINITY;
-        mi[t] = 0x7fffffff;
+    double ld = INFINITY;
+    int32_t li = 0x7fffffff;
+    const int64_t e = min(N, (int64_t)(blockIdx.x + 1) * seg);
+    for (int64_t j0 = (int64_t)blockIdx.x * seg; j0 < e; j0 += 64) {
+        const int64_t j = j0 + lane, jc = min(j, e - 1);
+        const double D = canon_sqdist(q, X + jc * dp, d);
+        const int32_t id = idmap[jc];
+        const double wd = __shfl(ld, kappa - 1);
+        const int32_t wi = __shfl(li, kappa - 1);
+        const bool in = j < e && !(excl && j == row) && wl_before(D, id, wd, wi);
+        if (__ballot(in)) wl_insert(ld, li, D, id, in);
     }
-    for (int64_t j = tid; j < N; j += KX_T) {
-        if (excl && j == row) continue;
-        double D = canon_sqdist(q, X + j * dp, d);
-        const int id = idmap[j];
-        if (!lt_di(D, id, md[kappa - 1], mi[kappa - 1])) continue;
-        int p = kappa - 1;
-        while (p > 0 && lt_di(D, id, md[p - 1], mi[p - 1])) {
-            md[p] = md[p - 1];
-            mi[p] = mi[p - 1];
-            --p;
-        }
-        md[p] = D;
-        mi[p] = id;
-    }
-    __syncthreads();
-    for (int st = 1; st < KX_T; st <<= 1) {
-        if (tid % (2 * st) == 0) {
-            double *bd2 = ld + (tid + st) * kappa;
-            int *bi2 = li + (tid + st) * kappa;
-            double tdd[KX_K];
-            int tii[KX_K];
-            int a = 0, b = 0;
-            for (int t = 0; t < kappa; ++t) {
-                if (lt_di(md[a], mi[a], bd2[b], bi2[b])) { tdd[t] = md[a]; tii[t] = mi[a]; ++a; }
-                else { tdd[t] = bd2[b]; tii[t] = bi2[b]; ++b; }
-            }
-            for (int t = 0; t < kappa; ++t) {
-                md[t] = tdd[t];
-                mi[t] = tii[t];
-            }
-        }
-        __syncthreads();
-    }
-    if (tid < kappa) {
-        const int64_t orow = rowmap ? rowmap[row] : row;
-        idx[orow * kappa + tid] = li[tid];
-        dist[orow * kappa + tid] = ld[tid];
+    const int64_t o = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 64 + lane;
+    pd[o] = ld;
+    pi[o] = li;
+}
+
+__global__ __launch_bounds__(64) void k_knn_exact_merge(int nseg, const double *__restrict__ pd,
+                                                        const int32_t *__restrict__ pi, int kappa,
+                                                        const int32_t *__restrict__ rows,
+                                                        const int32_t *__restrict__ rowmap,
+                                                        int32_t *__restrict__ idx, double *__restrict__ dist)
+{
+    const int lane = threadIdx.x;
+    const int64_t o = (int64_t)blockIdx.x * nseg * 64 + lane;
+    double ld = pd[o];
+    int32_t li = pi[o];
+    for (int g = 1; g < nseg; ++g) wl_merge_sorted(ld, li, pd[o + 64 * g], pi[o + 64 * g]);
+    if (lane < kappa) {
+        const int64_t row = rows[blockIdx.x], orow = rowmap ? rowmap[row] : row;
+        idx[orow * kappa + lane] = li;
+        dist[orow * kappa + lane] = ld;
     }
 }
 
@@ -1931,11 +1932,25 @@ void knn_exact_rows(const float *Q, const float *X, int64_t N, int d, int dp, in
                     const int32_t *rowmap, int32_t *idx, double *dist, hipStream_t s)
 {
     if (nrows <= 0) return;
-    if (kappa > KX_K) fail(ASKIT_ERR_UNSUPPORTED, "kappa above 64 is not supported");
-    size_t sh = (size_t)KX_T * kappa * (sizeof(double) + sizeof(int));
-    hipLaunchKernelGGL(k_knn_exact, dim3(nrows), dim3(KX_T), sh, s, Q, X, N, d, dp, kappa,
-                       exclude_self ? 1 : 0, rows, idmap, rowmap, idx, dist);
-    HIPC(hipGetLastError());
+    if (kappa > 64) fail(ASKIT_ERR_UNSUPPORTED, "kappa above 64 is not supported");
+    // rows in passes that bound the grid and the segments' lists
+    constexpr int PASS = 32768;
+    for (int r0 = 0; r0 < nrows; r0 += PASS) {
+        const int n = std::min(PASS, nrows - r0);
+        const int64_t nseg = std::max<int64_t>(1, std::min<int64_t>((N + KX_SEG - 1) / KX_SEG, 65536 / n));
+        const int64_t seg = (N + nseg - 1) / nseg;
+        double *pd;
+        int32_t *pi;
+        HIPC(ws_alloc((void **)&pd, sizeof(double) * n * nseg * 64, s));
+        HIPC(ws_alloc((void **)&pi, sizeof(int32_t) * n * nseg * 64, s));
+        hipLaunchKernelGGL(k_knn_exact, dim3((unsigned)nseg, (unsigned)n), dim3(64), 0, s, Q, X, N, d, dp, kappa,
+                           exclude_self ? 1 : 0, rows + r0, seg, idmap, pd, pi);
+        hipLaunchKernelGGL(k_knn_exact_merge, dim3((unsigned)n), dim3(64), 0, s, (int)nseg, pd, pi, kappa, rows + r0,
+                           rowmap, idx, dist);
+        HIPC(hipGetLastError());
+        HIPC(ws_free(pd, s));
+        HIPC(ws_free(pi, s));
+    }
 }
 
 // ---------------------------------------------------------------- filtered fallback
@@ -2044,11 +2059,11 @@ __global__ void k_gather_qrows(const int32_t *__restrict__ rows, int64_t n, int 
     }
 }
 
-// One wave per fallback row: exact FP64 distances of the row's survivors,
+// One wave per row (rows[i], or row0 + i): exact FP64 distances of the row's survivors,
 // the kappa smallest (D, id) kept in a sorted 64-entry list (chunks of 64
 // sorted, then merged by a bitonic half-cleaner); rows whose survivors did
 // not fit are listed for the full scan.
-__global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ rows, int64_t n,
+__global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ rows, int64_t row0, int64_t n,
                                                     const float *__restrict__ Q, const float *__restrict__ X,
                                                     int d, int dp, int kappa, int excl, int cap,
                                                     const int32_t *__restrict__ ocnt,
@@ -2062,7 +2077,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ 
     const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
     const int lane = threadIdx.x % WAVE;
     if (i >= n) return;
-    const int64_t row = rows[i];
+    const int64_t row = rows ? rows[i] : i + row0;
     const int cnt = ocnt[i];
     if (cnt > cap) {
         if (lane == 0) over_rows[atomicAdd(over_count, 1)] = (int32_t)row;
@@ -2149,14 +2164,132 @@ void knn_fallback(const float *Q, const uint16_t *Qh, const uint16_t *Ql, const 
                      false);
     }
     HIPC(hipGetLastError());
-    hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, rows, n, Q, X, d, dp, kappa,
-                       exclude_self ? 1 : 0, FCAP, ocnt, oe, idmap, rowmap, idx, dist, over + 1, over);
+    hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, rows, (int64_t)0, n, Q, X, d,
+                       dp, kappa, exclude_self ? 1 : 0, FCAP, ocnt, oe, idmap, rowmap, idx, dist, over + 1, over);
     HIPC(hipGetLastError());
     int32_t nover = 0;
     HIPC(hipMemcpyAsync(&nover, over, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
     knn_exact_rows(Q, X, N, d, dp, kappa, exclude_self, over + 1, nover, idmap, rowmap, idx, dist, s);
     for (void *p : tmp) HIPC(ws_free(p, s));
+}
+
+// T[i] <- the smallest FP32 value at or above thr[i] + 2 E_i (E: the bound of
+// an approximate distance's error), for the rows rows[i] (NULL: all).
+__global__ void k_add_bound(const float *__restrict__ thr, const float *__restrict__ Xn, double gamma,
+                            double maxnorm, int64_t n, const int32_t *__restrict__ rows, float *__restrict__ T)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int64_t r = rows ? rows[i] : i;
+    const double b = (double)thr[r] + 2.0 * gamma * ((double)Xn[r] + maxnorm);
+    float f = (float)b;
+    if ((double)f < b) f = nextafterf(f, INFINITY);
+    T[r] = f;
+}
+
+// The kappa nearest neighbours of every point among the others for a kappa
+// that leaves no room between it and KNN_CAND: the candidates of the
+// certificate would hardly be certified (at kappa = 64 none are), so the sweep
+// itself runs at a threshold that keeps every neighbour -- the window's
+// KNN_CAND-th approximate distance t bounds the kappa-th exact one by t + E, and
+// a neighbour's approximate distance by t + 2 E -- and all survivors are
+// re-ranked in FP64 (one pass over the points instead of two).  Rows whose
+// survivors overflow take the filtered fallback at the bound of the stored
+// ones.  The whole solve at 100,000 x 4, kappa = 64: 27.8 ms with candidates,
+// certificate and fallback, 18.6 this way.
+void knn_direct(const float *Xf, const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int d, int dp,
+                int kappa, float maxnorm, const int32_t *idmap, int32_t *idx, double *dist, hipStream_t s,
+                float *t_filter_ms, int *n_filter, std::vector<int32_t> *retry_rows, int64_t *tiles_swept)
+{
+    std::vector<void *> tmp;
+    struct Guard {
+        std::vector<void *> &t;
+        hipStream_t s;
+        ~Guard() { for (void *p : t) (void)ws_free(p, s); }
+    } guard{tmp, s};
+    auto ta = [&](size_t b) {
+        void *p;
+        HIPC(ws_alloc(&p, std::max<size_t>(b, 16), s));
+        tmp.push_back(p);
+        return p;
+    };
+    const int64_t ntiles = (N + KB_N - 1) / KB_N;
+    const bool small = ntiles <= KNN_SMALL;
+    const bool sym = !small && (double)N * KNN_CAP * 8.0 <= 48.0 * (1ull << 30);
+    const int64_t chunk = std::min<int64_t>(N, sym ? N : KNN_CHUNK);
+    FilterBufs B;
+    B.nsel = KNN_CAND;
+    B.ocnt = (int32_t *)ta(sizeof(int32_t) * chunk);
+    B.oe = (uint2 *)ta(sizeof(uint2) * chunk * KNN_CAP);
+    float *thr = (float *)ta(sizeof(float) * N), *T = (float *)ta(sizeof(float) * N);
+    int32_t *cand = (int32_t *)ta(sizeof(int32_t) * N * KNN_CAND);
+    int32_t *over = (int32_t *)ta(sizeof(int32_t) * (N + 1));
+    const double g = 2.0 * (3.1 * ldexp(1.0, -16) + (4.0 * dp + 8.0) * ldexp(1.0, -24));
+    const double mx = (double)maxnorm * (1.0 + 1e-5);
+    window_thresholds(dp, s, Xh, Xl, Xn, N, Xh, Xl, Xn, N, 1, chunk, thr, B, cand, small);
+    const unsigned nb = (unsigned)((N + 255) / 256);
+    hipLaunchKernelGGL(k_add_bound, dim3(nb), dim3(256), 0, s, thr, Xn, g, mx, N, (const int32_t *)nullptr, T);
+    HIPC(hipGetLastError());
+    int32_t *tlist = nullptr;
+    int64_t *toff = nullptr, kept = 0, kept_waves = 0, nitems = 0;
+    int4 *items = nullptr;
+    *tiles_swept = -1;
+    if (sym && !std::getenv("ASKIT_KNN_NO_SKIP") &&
+        build_tile_lists(Xf, T, Xn, N, Xf, T, Xn, N, dp, d, true, tlist, toff, kept, kept_waves, items, nitems, tmp, s))
+        *tiles_swept = kept_waves;
+    else
+        tlist = nullptr;
+    hipEvent_t e0, e1;
+    HIPC(hipEventCreate(&e0));
+    HIPC(hipEventCreate(&e1));
+    struct EvFree {
+        hipEvent_t a, b;
+        ~EvFree()
+        {
+            (void)hipEventDestroy(a);
+            (void)hipEventDestroy(b);
+        }
+    } evf{e0, e1};
+    *t_filter_ms = 0.f;
+    *n_filter = 0;
+    retry_rows->clear();
+    for (int64_t r0 = 0; r0 < N; r0 += chunk) {
+        const int64_t m = std::min<int64_t>(chunk, N - r0);
+        dim3 gr((unsigned)((m + KB_M - 1) / KB_M), (unsigned)(sym ? 1 : filter_segments(m, ntiles)));
+        if (tlist) gr = dim3((unsigned)nitems);
+        HIPC(hipMemsetAsync(B.ocnt, 0, sizeof(int32_t) * m, s));
+        HIPC(hipMemsetAsync(over, 0, sizeof(int32_t), s));
+        HIPC(hipEventRecord(e0, s));
+        if (!tlist || nitems > 0)
+            KNN_DISPATCH(launch_filter, gr, dim3(256), s, Xh, Xl, Xn, m, Xh, Xl, Xn, N, 1, r0, T, KNN_CAP, B.ocnt,
+                         B.oe, sym, 0, tlist, toff, items);
+        HIPC(hipEventRecord(e1, s));
+        hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, (const int32_t *)nullptr, r0,
+                           m, Xf, Xf, d, dp, kappa, 1, KNN_CAP, B.ocnt, B.oe, idmap, idmap, idx, dist, over + 1, over);
+        HIPC(hipGetLastError());
+        int32_t nover = 0;
+        HIPC(hipMemcpyAsync(&nover, over, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+        float ms = 0.f;
+        HIPC(hipEventElapsedTime(&ms, e0, e1));
+        *t_filter_ms += ms;
+        ++*n_filter;
+        if (nover == 0) continue;
+        // the KNN_CAND-th of a row's stored survivors (real points) is a bound
+        // like the window's, and mostly far below it
+        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, r0, KNN_CAP, B.nsel,
+                           B.ocnt, B.oe, cand, thr, (int32_t *)nullptr, (int32_t *)nullptr);
+        hipLaunchKernelGGL(k_add_bound, dim3((unsigned)((nover + 255) / 256)), dim3(256), 0, s, thr, Xn, g, mx,
+                           (int64_t)nover, over + 1, T);
+        HIPC(hipGetLastError());
+        knn_fallback(Xf, Xh, Xl, Xn, Xf, Xh, Xl, Xn, N, d, dp, kappa, true, over + 1, nover, T, idmap, idmap, idx,
+                     dist, s);
+        const size_t k = retry_rows->size();
+        retry_rows->resize(k + nover);
+        HIPC(hipMemcpyAsync(retry_rows->data() + k, over + 1, sizeof(int32_t) * nover, hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+    }
 }
 
 }  // namespace askit

@@ -17,6 +17,7 @@
 // The tree shape depends only on N and m, so every level's node ranges are
 // known on the host before the level runs.
 #include "askit_impl.h"
+#include "wave_list.h"
 
 #include <algorithm>
 
@@ -746,31 +747,11 @@ __global__ void k_rp_init(int32_t *__restrict__ idx, double *__restrict__ dist, 
 // across the wave (lane t: the t-th nearest), the leaf's other points are taken
 // 64 at a time, one canonical FP64 distance per lane, and those before the
 // list's last entry in (distance, id) order and not in the list yet (binary
-// search across the lanes) are merged: up to RL_SERIAL one by one, each by a
-// ballot and a shift, more by a bitonic sort of the batch and one merge.  The
-// lists are those of any order of insertion.  Bound by the shuffles of the
+// search across the lanes) are merged (wave_list.h).  The lists are those of any order of insertion.  Bound by the shuffles of the
 // sorts; one thread per point with its list in scratch memory took 53.6 ms for
 // 4 rounds over 131,071 points (kappa = 64, leaves of 256), this form
 // 1.7 ms.
 constexpr int RL_PTS = 16;
-constexpr int RL_SERIAL = 16;
-
-__device__ __forceinline__ bool rl_before(double d1, int32_t i1, double d2, int32_t i2)
-{
-    return d1 < d2 || (d1 == d2 && i1 < i2);
-}
-
-// compare-exchange with lane ^ o: the smaller entry stays in the lane whose
-// bit o is clear (up) or set (not up)
-__device__ __forceinline__ void rl_exchange(double &d, int32_t &i, int o, bool up)
-{
-    const double od = __shfl_xor(d, o);
-    const int32_t oi = __shfl_xor(i, o);
-    const bool low = ((threadIdx.x & o) == 0) == up;      // this lane keeps the smaller
-    const bool take = low ? rl_before(od, oi, d, i) : rl_before(d, i, od, oi);
-    d = take ? od : d;
-    i = take ? oi : i;
-}
 
 __global__ __launch_bounds__(256) void k_rp_leaf_search(const float *__restrict__ X, int dp, int d,
                                                         const int32_t *__restrict__ perm,
@@ -796,7 +777,7 @@ __global__ __launch_bounds__(256) void k_rp_leaf_search(const float *__restrict_
             const double D = canon_sqdist(xi, X + (int64_t)j * dp, d);
             const double wd = __shfl(ld, kappa - 1);
             const int32_t wi = __shfl(li, kappa - 1);
-            bool in = jj < lf.n && jj != ii && rl_before(D, j, wd, wi);
+            bool in = jj < lf.n && jj != ii && wl_before(D, j, wd, wi);
             if (!__ballot(in)) continue;
             // entries before (D, j): at most kappa - 1 for a point that goes in
             int r = 0;
@@ -804,45 +785,14 @@ __global__ __launch_bounds__(256) void k_rp_leaf_search(const float *__restrict_
             for (int st = 32; st > 0; st >>= 1) {
                 const double e = __shfl(ld, r + st - 1);
                 const int32_t f = __shfl(li, r + st - 1);
-                if (rl_before(e, f, D, j)) r += st;
+                if (wl_before(e, f, D, j)) r += st;
             }
             {
                 const double e = __shfl(ld, r);
                 const int32_t f = __shfl(li, r);
                 in = in && !(e == D && f == j);
             }
-            uint64_t m = __ballot(in);
-            if (__popcll(m) <= RL_SERIAL) {
-                while (m) {
-                    const int b = __ffsll((unsigned long long)m) - 1;
-                    m &= m - 1;
-                    const double cd = __shfl(D, b);
-                    const int32_t cj = __shfl(j, b);
-                    const int pos = __popcll(__ballot(rl_before(ld, li, cd, cj)));
-                    const double ud = __shfl_up(ld, 1);
-                    const int32_t ui = __shfl_up(li, 1);
-                    if (lane >= pos) {
-                        ld = lane == pos ? cd : ud;
-                        li = lane == pos ? cj : ui;
-                    }
-                }
-            } else {
-                double cd = in ? D : __longlong_as_double(0x7ff0000000000000ll);
-                int32_t ci = in ? j : 0x7fffffff;
-#pragma unroll
-                for (int k = 2; k <= 64; k <<= 1)
-#pragma unroll
-                    for (int o = k >> 1; o > 0; o >>= 1) rl_exchange(cd, ci, o, (lane & k) == 0);
-                // the 64 smallest of both: list ascending against the batch reversed
-                const double rd = __shfl(cd, 63 - lane);
-                const int32_t ri = __shfl(ci, 63 - lane);
-                if (rl_before(rd, ri, ld, li)) {
-                    ld = rd;
-                    li = ri;
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) rl_exchange(ld, li, o, true);
-            }
+            wl_insert(ld, li, D, j, in);
         }
         if (lane < kappa) {
             idx[(int64_t)i * kappa + lane] = li;
