@@ -1392,20 +1392,93 @@ void skeletonize_multi(const std::vector<askit_handle *> &hs, hipStream_t s)
 // ---------------------------------------------------------------- upward pass
 // w~_alpha[t] = Wc[piv t] + sum_c P[t][c] Wc[piv k+c]; Wc = W(X_alpha) at a
 // leaf, [w~_left; w~_right] at an internal node.  One wave per (node, t).
-// Skeleton weights of row t of node a, columns [r0, r1): w~_t = w(S_t) +
-// sum_c P_tc w(R_c) (Alg. 3, the far field by skeletonization).  Each
-// column's sum runs over c = lane, lane + 64, ... as an fma chain per lane,
-// then a xor butterfly across the wave (every lane ends with the same total);
-// the columns are taken RT at a time so that their weight loads are in flight
-// together.  A column's arithmetic does not depend on RT, on the column range
-// or on the number of columns.
-template <int RT>
-__device__ __forceinline__ void upward_row(const Node &nd, int a, int t, int k, int nr, int kl,
-                                           const int32_t *__restrict__ pv, const float *__restrict__ Pt,
-                                           const float *__restrict__ Wt, float *__restrict__ Wsk, int smax, int R,
-                                           int r0, int r1)
+// Sum of A per-lane values over the wave, the values spread over the lanes:
+// lane l returns the total of v[l / (64 / A)].  Every total is the one an xor
+// butterfly over 32, 16, 8, 4, 2, 1 gives, bit for bit (the two operands of an
+// add only change sides); a step over two or more values keeps half of them
+// in each lane, so A values take A - 1 exchanges and not 6 A, and none of them
+// goes through LDS.
+__device__ __forceinline__ float xor4(float v)
 {
-    const int lane = threadIdx.x;
+    // 7 - i within eight lanes, then 3 - i within four
+    return __int_as_float(__builtin_amdgcn_mov_dpp(
+        __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, false), 0x1b, 0xf, 0xf, false));
+}
+
+template <int O>
+__device__ __forceinline__ float xor_f32(float v)
+{
+    if constexpr (O == 4) return xor4(v);
+    else return __int_as_float(row_move<O>(__float_as_int(v)));
+}
+
+// x + y exchanged over lane bit O: lanes without the bit get x's total, lanes with it y's
+template <int O>
+__device__ __forceinline__ float pair_sum(float x, float y, int lane)
+{
+    if constexpr (O == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else if constexpr (O == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        const bool up = lane & O;
+        return (up ? y : x) + xor_f32<O>(up ? x : y);
+    }
+}
+
+template <int A, int O>
+__device__ __forceinline__ void scatter_step(float *v, int lane)
+{
+    if constexpr (A > 1) {
+#pragma unroll
+        for (int i = 0; i < A / 2; ++i) v[i] = pair_sum<O>(v[i], v[i + A / 2], lane);
+    } else {
+        v[0] = pair_sum<O>(v[0], v[0], lane);
+    }
+}
+
+template <int A>
+__device__ __forceinline__ float wave_totals(float (&v)[A], int lane)
+{
+    constexpr auto half = [](int n) { return n > 1 ? n / 2 : 1; };
+    scatter_step<A, 32>(v, lane);
+    scatter_step<half(A), 16>(v, lane);
+    scatter_step<half(half(A)), 8>(v, lane);
+    scatter_step<half(half(half(A))), 4>(v, lane);
+    scatter_step<half(half(half(half(A)))), 2>(v, lane);
+    scatter_step<half(half(half(half(half(A))))), 1>(v, lane);
+    return v[0];
+}
+
+// Skeleton weights of node a (Alg. 3, the far field by skeletonization):
+// w~_t = w(S_t) + sum_c P_tc w(R_c) for the rows t0 .. t0 + 4 UP_RW and the
+// columns [r0, r1).  A column's sum runs over c = lane, lane + 64, ... as an
+// fma chain per lane, then over the wave in the order of an xor butterfly; its
+// arithmetic does not depend on RT, the column range or the number of columns.
+//
+// The pass is bound by how often P and the weights are fetched, by the LDS
+// reads and by the sums across the wave, not by its products.  The node's
+// non-skeleton weight rows of RT columns are therefore staged once for 16 to 32
+// rows, UP_CH of them at a time, a wave forms UP_RW rows from each value read,
+// with the rows of P loaded before the staging waits, and the sums go through
+// wave_totals.  One row at a time over a loop of column tiles and rows, with a
+// butterfly per column, took 1,376 us for 64 columns at 200,000 points, 32-d
+// (1,022 nodes, up to 256 skeleton points); this form takes 315 us.
+constexpr int UP_CH = 256;
+template <int RT>
+constexpr int UP_RW = RT == 16 ? 4 : 8;           // rows per wave
+
+template <int RT>
+__device__ __forceinline__ void upward_rows(const Node &nd, int a, int k, int nr, int kl,
+                                            const int32_t *__restrict__ pv, const float *__restrict__ Pa,
+                                            const float *__restrict__ Wt, float *__restrict__ Wsk, int smax,
+                                            int R, int r0, int r1, int t0, float *sW)
+{
+    constexpr int RW = UP_RW<RT>, A = RW * RT;
+    constexpr int LD = RT == 16 ? 20 : RT;        // 20: 16-byte reads of 16 lanes touch every bank once
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // row of column c of the node's block: its own points at a leaf, else the
     // children's skeleton rows (left first)
     auto wrow = [&](int c) -> const float * {
@@ -1413,149 +1486,100 @@ __device__ __forceinline__ void upward_row(const Node &nd, int a, int t, int k, 
         return c < kl ? Wsk + ((int64_t)nd.left * smax + c) * R
                       : Wsk + ((int64_t)nd.right * smax + (c - kl)) * R;
     };
-    const float *w0 = wrow(pv[t]);
-    for (int rt = r0; rt < r1; rt += RT) {
-        float acc[RT];
+    const int tw = t0 + wv * RW;
+    const int oi = lane / (64 / A);               // this lane's entry of the wave's RW x RT results
+    const int ot = tw + oi / RT;
+    for (int rt = r0 + blockIdx.z * RT; rt < r1; rt += gridDim.z * RT) {
+        const int oc = rt + oi % RT;
+        const bool out = ot < k && oc < r1 && lane % (64 / A) == 0;
+        const float w0 = out ? wrow(pv[ot])[oc] : 0.0f;
+        float acc[A];
 #pragma unroll
-        for (int j = 0; j < RT; ++j) acc[j] = 0.0f;
-#pragma unroll 2
-        for (int c = lane; c < nr; c += 64) {
-            const float pc = Pt[c];
-            const float *wr = wrow(pv[k + c]);
-            float wv[RT];
+        for (int i = 0; i < A; ++i) acc[i] = 0.0f;
+        for (int c0 = 0; c0 < nr; c0 += UP_CH) {
+            float pc[RW][UP_CH / 64];
 #pragma unroll
-            for (int j = 0; j < RT; ++j) wv[j] = wr[min(rt + j, r1 - 1)];   // clamped: unconditional loads
+            for (int q = 0; q < RW; ++q) {
+                const float *Pt = Pa + (int64_t)min(tw + q, k - 1) * nr;
 #pragma unroll
-            for (int j = 0; j < RT; ++j) acc[j] = fmaf(pc, wv[j], acc[j]);
+                for (int u = 0; u < UP_CH / 64; ++u) {
+                    const int c = c0 + 64 * u + lane;
+                    const float p = Pt[min(c, nr - 1)];
+                    pc[q][u] = c < nr ? p : 0.0f;
+                }
+            }
+            // columns past r1 take column r1 - 1 (their results are not written);
+            // eight loads at a time
+            __syncthreads();                      // the previous tile's reads are done
+            constexpr int SG = RT < 8 ? RT : 8;
+#pragma unroll
+            for (int g = 0; g < RT; g += SG) {
+                float st[SG];
+#pragma unroll
+                for (int u = 0; u < SG; ++u) {
+                    const int e = tid + 256 * (g + u), c = c0 + e / RT;
+                    st[u] = wrow(pv[k + min(c, nr - 1)])[min(rt + e % RT, r1 - 1)];
+                    if (c >= nr) st[u] = 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < SG; ++u) {
+                    const int e = tid + 256 * (g + u);
+                    sW[(e / RT) * LD + e % RT] = st[u];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < UP_CH / 64; ++u) {
+                if (c0 + 64 * u >= nr) break;
+                const float *w = sW + (64 * u + lane) * LD;
+                float wr[RT];
+                if constexpr (RT >= 4) {
+#pragma unroll
+                    for (int j = 0; j < RT; j += 4) *(float4 *)(wr + j) = *(const float4 *)(w + j);
+                } else {
+                    wr[0] = w[0];
+                }
+#pragma unroll
+                for (int q = 0; q < RW; ++q)
+#pragma unroll
+                    for (int j = 0; j < RT; ++j) acc[q * RT + j] = fmaf(pc[q][u], wr[j], acc[q * RT + j]);
+            }
         }
-#pragma unroll
-        for (int j = 0; j < RT; ++j) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o);
-        }
-        float v = acc[0];
-#pragma unroll
-        for (int j = 1; j < RT; ++j) v = lane == j ? acc[j] : v;
-        if (lane < RT && rt + lane < r1) Wsk[((int64_t)a * smax + t) * R + rt + lane] = w0[rt + lane] + v;
+        const float v = wave_totals(acc, lane);
+        if (out) Wsk[((int64_t)a * smax + ot) * R + oc] = w0 + v;
     }
 }
 
 template <int RT>
-__global__ __launch_bounds__(64) void k_upward(const Node *__restrict__ nodes,
-                                               const int32_t *__restrict__ ids,
-                                               const int32_t *__restrict__ skk,
-                                               const int32_t *__restrict__ ncols,
-                                               const int32_t *__restrict__ colperm, int ncol_max,
-                                               const int64_t *__restrict__ pslot,
-                                               const float *__restrict__ P, int smax,
-                                               const float *__restrict__ Wt, int R,
-                                               float *__restrict__ Wsk, int r0, int r1)
+__global__ __launch_bounds__(256, 3) void k_upward(const Node *__restrict__ nodes, const int32_t *__restrict__ ids,
+                                                const int32_t *__restrict__ skk,
+                                                const int32_t *__restrict__ ncols,
+                                                const int32_t *__restrict__ colperm, int ncol_max,
+                                                const int64_t *__restrict__ pslot, const float *__restrict__ P,
+                                                int smax, const float *__restrict__ Wt, int R,
+                                                float *__restrict__ Wsk, int r0, int r1)
 {
-    const int a = ids[blockIdx.x], t = blockIdx.y;
-    const int k = skk[a];
-    if (t >= k) return;
-    const Node nd = nodes[a];
-    const int nr = ncols[a] - k;
-    const int kl = nd.left >= 0 ? skk[nd.left] : 0;
-    upward_row<RT>(nd, a, t, k, nr, kl, colperm + (int64_t)a * ncol_max, P + pslot[a] + (int64_t)t * nr, Wt, Wsk,
-                   smax, R, r0, r1);
-}
-
-// The same rows of skeleton weights for many columns: one workgroup per
-// (node, UP_TT skeleton rows).  For each tile of RT columns the node's
-// non-skeleton weight rows are staged in LDS once, then the four waves take
-// the skeleton rows in turn.  Every column's arithmetic is that of
-// upward_row (fma chain over c = lane, lane + 64, ..., xor butterfly,
-// w(S_t) added last), so both forms give the same bits.
-constexpr int UP_TT = 64;
-
-template <int RT>
-__device__ __forceinline__ void upward_block(const Node &nd, int a, int k, int nr, int kl,
-                                             const int32_t *__restrict__ pv, const float *__restrict__ Pa,
-                                             const float *__restrict__ Wt, float *__restrict__ Wsk, int smax,
-                                             int R, int r0, int r1, int t0, int32_t *sPv, float *sW)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    auto wrow = [&](int c) -> const float * {
-        if (nd.left < 0) return Wt + (int64_t)(nd.lo + c) * R;
-        return c < kl ? Wsk + ((int64_t)nd.left * smax + c) * R
-                      : Wsk + ((int64_t)nd.right * smax + (c - kl)) * R;
-    };
-    for (int c = tid; c < nr; c += 256) sPv[c] = pv[k + c];
-    const int tn = min(UP_TT, k - t0);
-    const int ne = nr * RT;
-    for (int rt = r0; rt < r1; rt += RT) {
-        __syncthreads();
-        // rows c of the block, columns rt .. rt + RT (clamped: unconditional loads, four in flight)
-        for (int e0 = tid; e0 < ne; e0 += 256 * 4) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = min(e0 + 256 * u, ne - 1);
-                v[u] = wrow(sPv[e / RT])[min(rt + e % RT, r1 - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = e0 + 256 * u;
-                if (e < ne) sW[(e / RT) * (RT + 1) + e % RT] = v[u];
-            }
-        }
-        __syncthreads();
-        for (int tt = wv; tt < tn; tt += 4) {
-            const int t = t0 + tt;
-            const float *Pt = Pa + (int64_t)t * nr;
-            float acc[RT];
-#pragma unroll
-            for (int j = 0; j < RT; ++j) acc[j] = 0.0f;
-#pragma unroll 2
-            for (int c = lane; c < nr; c += 64) {
-                const float pc = Pt[c];
-                const float *wr = sW + c * (RT + 1);
-#pragma unroll
-                for (int j = 0; j < RT; ++j) acc[j] = fmaf(pc, wr[j], acc[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < RT; ++j) {
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o);
-            }
-            float v = acc[0];
-#pragma unroll
-            for (int j = 1; j < RT; ++j) v = lane == j ? acc[j] : v;
-            if (lane < RT && rt + lane < r1)
-                Wsk[((int64_t)a * smax + t) * R + rt + lane] = wrow(pv[t])[rt + lane] + v;
-        }
-    }
-}
-
-template <int RT>
-__global__ __launch_bounds__(256) void k_upward_blk(const Node *__restrict__ nodes,
-                                                    const int32_t *__restrict__ ids,
-                                                    const int32_t *__restrict__ skk,
-                                                    const int32_t *__restrict__ ncols,
-                                                    const int32_t *__restrict__ colperm, int ncol_max,
-                                                    const int64_t *__restrict__ pslot,
-                                                    const float *__restrict__ P, int smax,
-                                                    const float *__restrict__ Wt, int R,
-                                                    float *__restrict__ Wsk, int r0, int r1)
-{
-    extern __shared__ float usm[];
-    const int a = ids[blockIdx.x], t0 = blockIdx.y * UP_TT;
+    __shared__ __attribute__((aligned(16))) float sW[UP_CH * (RT == 16 ? 20 : RT)];
+    const int a = ids[blockIdx.x], t0 = blockIdx.y * 4 * UP_RW<RT>;
     const int k = skk[a];
     if (t0 >= k) return;
     const Node nd = nodes[a];
     const int nr = ncols[a] - k;
     const int kl = nd.left >= 0 ? skk[nd.left] : 0;
-    upward_block<RT>(nd, a, k, nr, kl, colperm + (int64_t)a * ncol_max, P + pslot[a], Wt, Wsk, smax, R, r0, r1,
-                     t0, (int32_t *)usm, usm + ncol_max);
+    upward_rows<RT>(nd, a, k, nr, kl, colperm + (int64_t)a * ncol_max, P + pslot[a], Wt, Wsk, smax, R, r0, r1, t0,
+                    sW);
 }
 
-// columns per tile of the upward pass for a range of nc columns
-static int upward_tile(int nc) { return nc >= 16 ? 16 : (nc >= 4 ? 4 : 1); }
+// columns per tile of the upward pass for a range of nc columns: the tile's
+// unused columns cost loads and products, a narrower tile reads P more often
+static int upward_tile(int nc) { return nc >= 8 ? 16 : (nc >= 2 ? 4 : 1); }
 
-// LDS of the block form for RT columns and blocks of up to ncol_max columns
-static size_t upward_lds(int RT, int ncol_max) { return sizeof(float) * (size_t)ncol_max * (RT + 2); }
-constexpr size_t UP_LDS_MAX = 64 * 1024;
+// (node, rows, column tiles)
+static dim3 upward_grid(int64_t nodes, int smax, int nc, int rt)
+{
+    const int rows = 4 * (rt == 16 ? UP_RW<16> : UP_RW<1>);
+    return dim3((unsigned)nodes, (unsigned)((smax + rows - 1) / rows), (unsigned)std::min((nc + rt - 1) / rt, 1024));
+}
 
 void prepare_upward(askit_handle *h)
 {
@@ -1573,69 +1597,47 @@ void prepare_upward(askit_handle *h)
 void upward(askit_handle *h, const WeightSet &ws, hipStream_t s, int r0, int r1)
 {
     if (r1 < 0) r1 = ws.R;
+    const int rt = upward_tile(r1 - r0);
+    const auto kern = rt == 16 ? k_upward<16> : rt == 4 ? k_upward<4> : k_upward<1>;
     for (auto &sg : h->up_seg) {
         if (sg.second == 0) continue;
-        const int rt = upward_tile(r1 - r0);
-        const size_t lds = upward_lds(rt, h->ncol_max);
-        const dim3 gb(sg.second, (h->smax + UP_TT - 1) / UP_TT), bb(256);
-        const dim3 g(sg.second, h->smax), b(64);
-        if (rt == 16 && lds <= UP_LDS_MAX)
-            hipLaunchKernelGGL(k_upward_blk<16>, gb, bb, lds, s, h->d_nodes, h->up_ids + sg.first, h->skk,
-                               h->ncols, h->colperm, h->ncol_max, h->d_pslot, h->P, h->smax, ws.Wt, ws.R, ws.Wsk,
-                               r0, r1);
-        else if (rt == 4 && lds <= UP_LDS_MAX)
-            hipLaunchKernelGGL(k_upward_blk<4>, gb, bb, lds, s, h->d_nodes, h->up_ids + sg.first, h->skk,
-                               h->ncols, h->colperm, h->ncol_max, h->d_pslot, h->P, h->smax, ws.Wt, ws.R, ws.Wsk,
-                               r0, r1);
-        else if (rt == 16)
-            hipLaunchKernelGGL(k_upward<16>, g, b, 0, s, h->d_nodes, h->up_ids + sg.first, h->skk, h->ncols,
-                               h->colperm, h->ncol_max, h->d_pslot, h->P, h->smax, ws.Wt, ws.R, ws.Wsk, r0, r1);
-        else if (rt == 4)
-            hipLaunchKernelGGL(k_upward<4>, g, b, 0, s, h->d_nodes, h->up_ids + sg.first, h->skk, h->ncols,
-                               h->colperm, h->ncol_max, h->d_pslot, h->P, h->smax, ws.Wt, ws.R, ws.Wsk, r0, r1);
-        else
-            hipLaunchKernelGGL(k_upward<1>, g, b, 0, s, h->d_nodes, h->up_ids + sg.first, h->skk, h->ncols,
-                               h->colperm, h->ncol_max, h->d_pslot, h->P, h->smax, ws.Wt, ws.R, ws.Wsk, r0, r1);
+        hipLaunchKernelGGL(kern, upward_grid(sg.second, h->smax, r1 - r0, rt), dim3(256), 0, s, h->d_nodes,
+                           h->up_ids + sg.first, h->skk, h->ncols, h->colperm, h->ncol_max, h->d_pslot, h->P,
+                           h->smax, ws.Wt, ws.R, ws.Wsk, r0, r1);
         HIPC(hipGetLastError());
     }
 }
 
-// Batched upward pass: the same computation as k_upward, one wave per
-// ((instance, node), t) with the instance's tables and weight offsets.
+// Batched upward pass: the same computation as k_upward with the instance's
+// tables and weight offsets, one workgroup per ((instance, node), rows).
 template <int RT>
-__global__ __launch_bounds__(64) void k_upward_multi(const UpInst *__restrict__ inst,
-                                                     const int2 *__restrict__ items, int R,
-                                                     const float *__restrict__ Wt_all,
-                                                     float *__restrict__ Wsk_all)
+__global__ __launch_bounds__(256, 3) void k_upward_multi(const UpInst *__restrict__ inst,
+                                                      const int2 *__restrict__ items, int R,
+                                                      const float *__restrict__ Wt_all,
+                                                      float *__restrict__ Wsk_all)
 {
+    __shared__ __attribute__((aligned(16))) float sW[UP_CH * (RT == 16 ? 20 : RT)];
     const int2 it = items[blockIdx.x];
     const UpInst &I = inst[it.x];
-    const int a = it.y, t = blockIdx.y;
+    const int a = it.y, t0 = blockIdx.y * 4 * UP_RW<RT>;
     const int k = I.skk[a];
-    if (t >= k) return;
+    if (t0 >= k) return;
     const Node nd = I.nodes[a];
     const int nr = I.ncols[a] - k;
     const int kl = nd.left >= 0 ? I.skk[nd.left] : 0;
-    upward_row<RT>(nd, a, t, k, nr, kl, I.colperm + (int64_t)a * I.ncol_max, I.P + I.pslot[a] + (int64_t)t * nr,
-                   Wt_all + I.wt_off * R, Wsk_all + I.wsk_off * R, I.smax, R, 0, R);
+    upward_rows<RT>(nd, a, k, nr, kl, I.colperm + (int64_t)a * I.ncol_max, I.P + I.pslot[a], Wt_all + I.wt_off * R,
+                    Wsk_all + I.wsk_off * R, I.smax, R, 0, R, t0, sW);
 }
 
 void upward_batch(const UpInst *inst, const int2 *items, const std::vector<std::pair<int64_t, int64_t>> &levels,
                   int smax, const float *Wt, float *Wsk, int R, hipStream_t s)
 {
+    const int rt = upward_tile(R);
+    const auto kern = rt == 16 ? k_upward_multi<16> : rt == 4 ? k_upward_multi<4> : k_upward_multi<1>;
     for (const auto &lv : levels) {
         if (lv.second == 0) continue;
-        const dim3 g((unsigned)lv.second, (unsigned)smax), b(64);
-        switch (upward_tile(R)) {
-        case 16:
-            hipLaunchKernelGGL(k_upward_multi<16>, g, b, 0, s, inst, items + lv.first, R, Wt, Wsk);
-            break;
-        case 4:
-            hipLaunchKernelGGL(k_upward_multi<4>, g, b, 0, s, inst, items + lv.first, R, Wt, Wsk);
-            break;
-        default:
-            hipLaunchKernelGGL(k_upward_multi<1>, g, b, 0, s, inst, items + lv.first, R, Wt, Wsk);
-        }
+        hipLaunchKernelGGL(kern, upward_grid(lv.second, smax, R, rt), dim3(256), 0, s, inst, items + lv.first, R, Wt,
+                           Wsk);
         HIPC(hipGetLastError());
     }
 }
