@@ -331,7 +331,7 @@ void query_points(askit_handle *h, const WeightSet &ws, const float *Y, int64_t 
         HIPC(hipMemcpyAsync(dseg, hseg.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice, s));
         HIPC(hipStreamSynchronize(s));         // hseg is released on return of this block
     }
-    sort_queries(h, nb, M, order, nbs, tmp, s, dseg);
+    sort_queries(h, nb, M, order, nbs, tmp, s, dseg, nseg);
     gather_rows(Yp, order, M, dp, Ys, s);
     int32_t *ptr, *node;
     uint64_t *mask;

@@ -350,14 +350,16 @@ void build_query_interactions(askit_handle *h, const int32_t *nb, int64_t M, Sla
 void gather_f64(const double *src, const int32_t *idx, int64_t n, double *dst, hipStream_t s);
 
 // queries sorted by (segment, leaf of the nearest source, index): order[M],
-// nb rows permuted; seg (device, M) gives each query's segment (NULL: one)
+// nb rows permuted; seg (device, M) gives each query's segment of nseg (NULL: one)
 void sort_queries(askit_handle *h, const int32_t *nb, int64_t M, int32_t *order, int32_t *nb_sorted,
-                  std::vector<void *> &tmp, hipStream_t s, const int32_t *seg = nullptr);
+                  std::vector<void *> &tmp, hipStream_t s, const int32_t *seg, int64_t nseg);
 
 // skel.hip
 void skeletonize(askit_handle *h, hipStream_t s);
-// Ascending bitonic sort of n2 (a power of two) 64-bit keys in place.
-void sort_u64_pow2(uint64_t *key, int64_t n2, hipStream_t s);
+// order[0 .. n): the indices of keys below nkeys in ascending key order, equal
+// keys in index order (pairs.hip; temporaries from ta).
+void order_by_key(const uint32_t *key, int64_t n, uint64_t nkeys, int32_t *order,
+                  const std::function<void *(size_t)> &ta, hipStream_t s);
 // The skeletons of several handles (same ell, s_max and tolerance) in one
 // pass over the tree levels: each kernel launched once per level for the
 // nodes of every handle.

@@ -542,6 +542,123 @@ __global__ __launch_bounds__(64 * NW) void k_interactions(const Node *__restrict
     }
 }
 
+// The same lists for a tree whose row masks fit in LDS (and without a level
+// restriction).  make_shape halves every node, so all levels above the deepest
+// are full: level l starts at node 2^l - 1 and, above the last two, a node's
+// children are 2a + 1 and 2a + 2.
+//
+// A workgroup sets bit r of the leaf of every neighbour of row r, ORs the masks
+// up the tree level by level, and reads both lists off them: a leaf's mask is its
+// near entry, the parent's mask without the node's own is its far entry.  Every
+// step is parallel over pairs or nodes; what bounds it is the latency of those
+// depth + 4 steps, hidden by the other slabs of the CU.  Sorting each row's
+// neighbours in one lane, walking their ancestors and searching them for every
+// node of the union is a serial chain of LDS reads: 5.3 ms for the 16,384 slabs
+// of 2^20 points (4,095 nodes, both modes), here 0.6 ms; for 17 new points against
+// 2^18 points 0.63 ms, here 0.015 ms.
+__global__ __launch_bounds__(256) void k_interactions_mask(const Node *__restrict__ nodes, int nn, int depth,
+                                                           const int32_t *__restrict__ leaf_of,
+                                                           const Slab *__restrict__ slabs,
+                                                           const int32_t *__restrict__ nbpos, int nnb, int mode,
+                                                           int32_t *__restrict__ cnt_near,
+                                                           int32_t *__restrict__ cnt_far,
+                                                           const int32_t *__restrict__ ptr, int64_t nslab,
+                                                           int32_t *__restrict__ out_node,
+                                                           uint64_t *__restrict__ out_mask,
+                                                           int32_t *__restrict__ cntw)
+{
+    extern __shared__ unsigned long long msk[];
+    __shared__ int wcnt[8];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t sl = blockIdx.x;
+    const Slab sb = slabs[sl];
+    for (int a = tid; a < nn; a += 256) msk[a] = 0;
+    __syncthreads();
+    const int np = sb.nrows * nnb;
+    const int32_t *src = nbpos + (int64_t)sb.row0 * nnb;
+    for (int t0 = tid; t0 < np; t0 += 4 * 256) {
+        int v[4], lf[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[min(t0 + 256 * u, np - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) lf[u] = leaf_of[max(v[u], 0)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = t0 + 256 * u;
+            if (t < np && v[u] >= 0) atomicOr(&msk[lf[u]], 1ull << (t / nnb));
+        }
+    }
+    __syncthreads();
+    const int last = (1 << depth) - 1;                // first node of the deepest level
+    for (int lev = depth - 1; lev >= 0; --lev) {
+        const int n0 = (1 << lev) - 1;
+        for (int a = n0 + tid; a < 2 * n0 + 1; a += 256) {
+            if (lev == depth - 1) {
+                const int l = nodes[a].left;
+                if (l >= 0) msk[a] = msk[l] | msk[l + 1];
+            } else {
+                msk[a] = msk[2 * a + 1] | msk[2 * a + 2];
+            }
+        }
+        __syncthreads();
+    }
+    // each wave takes a contiguous range of nodes, so that the entries keep node order
+    const int per = (nn + 255) / 256 * 64;
+    const int a0 = min(nn, wv * per), a1 = min(nn, a0 + per);
+    int64_t on = 0, of = 0;
+    if (mode) {
+        on = ptr[sl] + cntw[(sl * 4 + wv) * 2];
+        of = ptr[nslab + 1 + sl] + cntw[(sl * 4 + wv) * 2 + 1];
+    }
+    const int mid = (1 << max(depth - 1, 0)) - 1;     // first node that may be a leaf
+    int kn = 0, kf = 0;
+    for (int b = a0; b < a1; b += 64) {
+        const int a = b + lane;
+        const bool ok = a < a1;
+        uint64_t m = 0, f = 0;
+        bool leaf = false;
+        if (ok) {
+            m = msk[a];
+            leaf = a >= last || (a >= mid && nodes[a].left < 0);
+            if (a > 0) f = msk[a >= last ? nodes[a].parent : (a - 1) >> 1] & ~m;
+        }
+        const uint64_t bn = __ballot(leaf && m != 0), bf = __ballot(f != 0);
+        const uint64_t below = (1ull << lane) - 1;
+        if (mode) {
+            if (leaf && m) {
+                const int64_t o = on + kn + __popcll(bn & below);
+                out_node[o] = a;
+                out_mask[o] = m;
+            }
+            if (f) {
+                const int64_t o = of + kf + __popcll(bf & below);
+                out_node[o] = a;
+                out_mask[o] = f;
+            }
+        }
+        kn += __popcll(bn);
+        kf += __popcll(bf);
+    }
+    if (!mode) {
+        if (lane == 0) {
+            wcnt[wv] = kn;
+            wcnt[4 + wv] = kf;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            int an = 0, af = 0;
+            for (int u = 0; u < 4; ++u) {
+                cntw[(sl * 4 + u) * 2] = an;
+                cntw[(sl * 4 + u) * 2 + 1] = af;
+                an += wcnt[u];
+                af += wcnt[4 + u];
+            }
+            cnt_near[sl] = an;
+            cnt_far[sl] = af;
+        }
+    }
+}
+
 __global__ void k_nbpos_self(const int32_t *__restrict__ perm, const int32_t *__restrict__ iperm,
                              const int32_t *__restrict__ knn_idx, int64_t N, int kappa,
                              int32_t *__restrict__ nb)
@@ -575,17 +692,27 @@ static void run_interactions(askit_handle *h, const Slab *d_slabs, int64_t nslab
                              std::vector<void *> &owned, hipStream_t s, bool persistent)
 {
     int nn = (int)h->nodes.size();
-    size_t shb = sizeof(uint32_t) * ((nn + 31) / 32) + sizeof(int32_t) * 64 * nnb;
+    // The mask form needs 8 bytes of LDS per node: up to 64 KB two workgroups fit
+    // on a CU and it is ahead everywhere it was timed (0.63 -> 0.015 ms at 1,023
+    // nodes, 5.3 -> 0.6 ms at 4,095).  Larger trees, and trees with a level
+    // restriction, whose far nodes come from descents, are scanned per union node.
+    const bool by_mask = nn <= 8192 && h->minlev <= 1;
+    const size_t shb = by_mask ? sizeof(uint64_t) * nn
+                               : sizeof(uint32_t) * ((nn + 31) / 32) + sizeof(int32_t) * 64 * nnb;
     if (shb > 150 * 1024) fail(ASKIT_ERR_UNSUPPORTED, "tree too large for the interaction kernel");
     // few slabs (a batch of new points): four waves share each slab's node scan
-    const bool wide = nslab < 2048;
-    const void *kfn = wide ? (const void *)k_interactions<4> : (const void *)k_interactions<1>;
+    const bool wide = by_mask || nslab < 2048;
+    const void *kfn = by_mask ? (const void *)k_interactions_mask
+                              : wide ? (const void *)k_interactions<4> : (const void *)k_interactions<1>;
     if (shb > 64 * 1024) HIPC(hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shb));
     int32_t *cnt, *cntw = nullptr;
     HIPC(ws_alloc((void **)&cnt, sizeof(int32_t) * 2 * (nslab + 1), s));
     if (wide) HIPC(ws_alloc((void **)&cntw, sizeof(int32_t) * 2 * 4 * std::max<int64_t>(nslab, 1), s));
     auto launch = [&](int mode, int32_t *cn, int32_t *cf, const int32_t *pp, int32_t *on, uint64_t *om) {
-        if (wide)
+        if (by_mask)
+            hipLaunchKernelGGL(k_interactions_mask, dim3((unsigned)nslab), dim3(256), shb, s, h->d_nodes, nn, h->depth,
+                               h->leaf_of, d_slabs, nbpos, nnb, mode, cn, cf, pp, nslab, on, om, cntw);
+        else if (wide)
             hipLaunchKernelGGL(k_interactions<4>, dim3((unsigned)nslab), dim3(256), shb, s, h->d_nodes, nn,
                                h->leaf_of, d_slabs, nbpos, nnb, mode, cn, cf, pp, nslab, on, om, cntw,
                                h->minlev);
@@ -668,40 +795,15 @@ void count_pairs(askit_handle *h, hipStream_t s)
 
 // ---- query grouping: sort queries by (leaf of their nearest source, index) so
 // that a slab holds spatially close targets (denser masks, small centred norms).
-// Sort key of query i: (its segment, the leaf of its nearest source, i); a
+// Sort key of query i: (its segment, the leaf of its nearest source); a
 // segment is one request of a served batch (seg NULL: one segment).
 __global__ void k_qkeys(const int32_t *__restrict__ nb, int64_t M, int kappa,
                         const int32_t *__restrict__ leaf_of, const int32_t *__restrict__ seg, int64_t nn,
-                        int64_t M2, uint64_t *__restrict__ key)
+                        uint32_t *__restrict__ key)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M2) return;
-    if (i >= M) {
-        key[i] = ~0ull;
-        return;
-    }
-    const uint64_t hi = (uint64_t)(uint32_t)leaf_of[nb[i * kappa]] + (seg ? (uint64_t)seg[i] * (uint64_t)nn : 0ull);
-    key[i] = (hi << 32) | (uint64_t)i;
-}
-
-__global__ void k_bitonic_step(uint64_t *__restrict__ key, int64_t M2, int64_t j, int64_t k)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= M2 / 2) return;
-    int64_t i = 2 * t - (t & (j - 1));
-    int64_t q = i + j;
-    bool up = (i & k) == 0;
-    uint64_t a = key[i], b = key[q];
-    if (up ? a > b : a < b) {
-        key[i] = b;
-        key[q] = a;
-    }
-}
-
-__global__ void k_qorder(const uint64_t *__restrict__ key, int64_t M, int32_t *__restrict__ order)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) order[i] = (int32_t)(key[i] & 0xffffffffull);
+    if (i >= M) return;
+    key[i] = (uint32_t)((uint64_t)(uint32_t)leaf_of[nb[i * kappa]] + (seg ? (uint64_t)seg[i] * (uint64_t)nn : 0ull));
 }
 
 __global__ void k_gather_i32_rows(const int32_t *__restrict__ src, const int32_t *__restrict__ idx,
@@ -713,27 +815,20 @@ __global__ void k_gather_i32_rows(const int32_t *__restrict__ src, const int32_t
     dst[t] = src[(int64_t)idx[row] * w + (t - row * w)];
 }
 
-void sort_u64_pow2(uint64_t *key, int64_t n2, hipStream_t s)
-{
-    for (int64_t k = 2; k <= n2; k <<= 1)
-        for (int64_t j = k >> 1; j > 0; j >>= 1)
-            hipLaunchKernelGGL(k_bitonic_step, dim3((unsigned)((n2 / 2 + 255) / 256)), dim3(256), 0, s, key, n2, j,
-                               k);
-    HIPC(hipGetLastError());
-}
-
 void sort_queries(askit_handle *h, const int32_t *nb, int64_t M, int32_t *order, int32_t *nb_sorted,
-                  std::vector<void *> &tmp, hipStream_t s, const int32_t *seg)
+                  std::vector<void *> &tmp, hipStream_t s, const int32_t *seg, int64_t nseg)
 {
-    int64_t M2 = 1;
-    while (M2 < M) M2 <<= 1;
-    uint64_t *key;
-    HIPC(ws_alloc((void **)&key, sizeof(uint64_t) * M2, s));
-    tmp.push_back(key);
-    hipLaunchKernelGGL(k_qkeys, dim3((unsigned)((M2 + 255) / 256)), dim3(256), 0, s, nb, M, h->kappa,
-                       h->leaf_of, seg, (int64_t)h->nodes.size(), M2, key);
-    sort_u64_pow2(key, M2, s);
-    hipLaunchKernelGGL(k_qorder, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, key, M, order);
+    auto ta = [&](size_t b) {
+        void *p;
+        HIPC(ws_alloc(&p, std::max<size_t>(b, 16), s));
+        tmp.push_back(p);
+        return p;
+    };
+    uint32_t *key = (uint32_t *)ta(sizeof(uint32_t) * M);
+    hipLaunchKernelGGL(k_qkeys, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, nb, M, h->kappa,
+                       h->leaf_of, seg, (int64_t)h->nodes.size(), key);
+    HIPC(hipGetLastError());
+    order_by_key(key, M, (uint64_t)h->nodes.size() * (uint64_t)nseg, order, ta, s);
     int64_t tot = M * h->kappa;
     hipLaunchKernelGGL(k_gather_i32_rows, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, nb,
                        order, M, h->kappa, nb_sorted);
