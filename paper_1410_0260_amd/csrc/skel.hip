@@ -413,6 +413,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
     __shared__ int piv[QR_MAXCOL];            // position -> column
     __shared__ double cd[W][RMAX];            // the W candidates' rows
     __shared__ double rdiag[RMAX];            // R_tt of the steps taken
+    __shared__ double svr[RMAX];              // the reflector's rows below t
     __shared__ double cv[W];
     __shared__ int32_t ck[W];
     __shared__ double rdv[NG];
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
             for (int r = 0; r < RM; ++r) {
                 const int i = l16 + 16 * r;
                 x[j][r] = (act[j] && i < rows) ? G[(int64_t)c * ell + i] : 0.0;
-                if (i < rows) sq += x[j][r] * x[j][r];
+                if (i < rows) sq = fma(x[j][r], x[j][r], sq);
             }
             nv[j] = group16_sum(sq);
         }
@@ -601,47 +602,51 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
                     act[j] = false;
                 }
             }
-            // the reflector H = I - c u u^T (u_t = x_t - R_tt, the column's rows
-            // below t as they are, c = -1 / (R_tt u_t)), alike in every workgroup
+            // the reflector, alike in every workgroup
             const double *vs = cd[pw];
             const double x0 = vs[t];
-            const double rtt = x0 >= 0.0 ? -nrm : nrm, ut = x0 - rtt;
-            const double cu = -1.0 / (rtt * ut);
+            const double rtt = x0 >= 0.0 ? -nrm : nrm;
+            const double denom = x0 - rtt, beta = (rtt - x0) / rtt;
             if (tid == 0) rdiag[t] = rtt;
             const int rt = t / 16, tl = t - l16;       // row l16 + 16 r is below t where 16 r > tl
+            if (tid < RMAX) svr[tid] = (tid > t && tid < rows) ? vs[tid] / denom : 0.0;
+            __syncthreads();
             double u[RM];
 #pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                const double z = vs[l16 + 16 * r];
-                u[r] = 16 * r > tl ? z : 16 * r == tl ? ut : 0.0;
-            }
+            for (int r = 0; r < RM; ++r) u[r] = svr[l16 + 16 * r];
+            const int src = (lane & 48) | (t & 15);    // the group's lane that holds row t
             if constexpr (TIMING) c5 = clock64();
             // JB columns at a time; slices above rt hold rows of R (uniform skip)
             constexpr int JB = CPG < 4 ? CPG : 4;
 #pragma unroll
             for (int j0 = 0; j0 < CPG; j0 += JB) {
-                double sd[JB], ns[JB];
+                double sd[JB], ns[JB], top[JB];
 #pragma unroll
-                for (int j = 0; j < JB; ++j) sd[j] = ns[j] = 0.0;
-#pragma unroll
-                for (int r = 0; r < RM; ++r) {
-                    if (r < rt) continue;
-#pragma unroll
-                    for (int j = 0; j < JB; ++j) sd[j] += u[r] * x[j0 + j][r];
-                }
-#pragma unroll
-                for (int j = 0; j < JB; ++j) sd[j] = group16_sum(sd[j]);
-#pragma unroll
-                for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? cu * sd[j] : 0.0;   // pivoted: rows kept
+                for (int j = 0; j < JB; ++j) sd[j] = ns[j] = top[j] = 0.0;
 #pragma unroll
                 for (int r = 0; r < RM; ++r) {
                     if (r < rt) continue;
 #pragma unroll
                     for (int j = 0; j < JB; ++j) {
-                        const double y = x[j0 + j][r] - sd[j] * u[r];
+                        if (r == rt) top[j] = __shfl(x[j0 + j][r], src);
+                        sd[j] = fma(u[r], x[j0 + j][r], sd[j]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] = group16_sum(sd[j]);
+#pragma unroll
+                for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? beta * (sd[j] + top[j]) : 0.0;   // pivoted: rows kept
+#pragma unroll
+                for (int r = 0; r < RM; ++r) {
+                    if (r < rt) continue;
+                    // row t itself: u_t = 1
+                    const double ur = r > rt ? u[r] : 16 * r == tl ? 1.0 : u[r];
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) {
+                        const double y = fma(-sd[j], ur, x[j0 + j][r]);
                         x[j0 + j][r] = y;
-                        if (r > rt) ns[j] += y * y;
-                        else ns[j] += 16 * r > tl ? y * y : 0.0;
+                        const double z = r > rt || 16 * r > tl ? y : 0.0;
+                    ns[j] = fma(z, z, ns[j]);
                     }
                 }
 #pragma unroll
@@ -694,15 +699,17 @@ __global__ __launch_bounds__(QG_T) void k_qrcp_gang(double *__restrict__ Gall, i
 // The factorization of a node whose columns fit one workgroup's registers
 // (cols <= T / 16 CPG, rows <= 16 RM): 16-lane group g keeps columns g + T / 16 j
 // in slot j, lane l16 rows l16 + 16 r, so G is read and written once and a pivot
-// step exchanges only the best column through LDS, with two barriers.  The pivot
-// rule, the swaps and the rank rule are k_qrcp's; the reflector H = I - c u u^T
-// is applied unscaled (u_t = G_tt - R_tt, u_i = G_it, c = -1 / (R_tt u_t)): one
-// quotient per step, and row t is an entry like the others.  Sums across lanes
-// are DPP steps (no LDS round trip).  Bound by the latency of a step's chain
-// (argmax, square root, quotient, two barriers, two sums over the lanes)
-// and the FP64 updates (3 FMA per held entry and step; slices above row t are
-// skipped).  100,000 points, m = 256, s = 128, l = 148: 15.4 ms with k_qrcp,
-// which streams G from memory every step, 6.2 ms here.
+// step exchanges only the best column through LDS, with three barriers.  The pivot
+// rule, the swaps, the rank rule and every sum are k_qrcp's, bit for bit (a
+// rank-deficient node's last pivots are decided by rounding): lane l16 adds
+// the rows of one residue mod 16 in ascending order there too, and the steps
+// across lanes commute with the rotation of the lanes.  Row t takes part in the
+// update with a reflector entry of 1.  Sums across lanes are DPP steps (no LDS
+// round trip).  Bound by the latency of a step's chain (argmax, square root,
+// two quotients, three barriers, two sums over the lanes) and the FP64 updates
+// (3 FMA per held entry and step; slices above row t are skipped).  100,000
+// points, m = 256, s = 128, l = 148: 15.4 ms with k_qrcp, which streams G from
+// memory every step, 6.6 ms here.
 constexpr int QR_PAD = 160;                  // 16 RM at most
 
 template <int T, int RM, int CPG, int JB>
@@ -714,6 +721,7 @@ __global__ __launch_bounds__(T) void k_qrcp_reg(double *__restrict__ Gall, int e
     static_assert(NG == 16 || NG == 32 || NG == 64, "every lane of a row takes NG / 16 of the groups' best");
     static_assert(16 * RM <= QR_PAD && CPG % JB == 0, "padding of G, whole blocks of columns");
     __shared__ double buf[16 * RM];           // the pivot column
+    __shared__ double svr[16 * RM];           // the reflector's rows below t
     __shared__ double rdiag[16 * RM];         // R_tt of the steps taken
     __shared__ double rdv[NG];
     __shared__ int32_t rdk[NG];
@@ -749,7 +757,7 @@ __global__ __launch_bounds__(T) void k_qrcp_reg(double *__restrict__ Gall, int e
         for (int r = 0; r < RM; ++r) {
             asm volatile("" : "+v"(x[j][r]));              // (not sunk into branches)
             x[j][r] = (act[j] && 16 * r < rows - l16) ? x[j][r] : 0.0;
-            nv[j] += x[j][r] * x[j][r];
+            nv[j] = fma(x[j][r], x[j][r], nv[j]);
         }
         nv[j] = group16_sum(nv[j]);
     }
@@ -814,45 +822,55 @@ __global__ __launch_bounds__(T) void k_qrcp_reg(double *__restrict__ Gall, int e
         }
         __syncthreads();
         const double x0 = buf[t];
-        const double rtt = x0 >= 0.0 ? -nrm : nrm, ut = x0 - rtt;
+        const double rtt = x0 >= 0.0 ? -nrm : nrm;
         if (tid == 0) {
             piv[t] = pc;
             piv[pp] = ct;
             rdiag[t] = rtt;
         }
-        const double c = -1.0 / (rtt * ut);
+        const double denom = x0 - rtt, beta = (rtt - x0) / rtt;
         const int tl = t - l16;                    // row l16 + 16 r is below t where 16 r > tl
-        double u[RM];
-#pragma unroll
-        for (int r = 0; r < RM; ++r) {
-            const double z = buf[l16 + 16 * r];
-            u[r] = 16 * r > tl ? z : 16 * r == tl ? ut : 0.0;
-        }
+        if (tid < 16 * RM) svr[tid] = tid > t ? buf[tid] / denom : 0.0;
+        __syncthreads();
+        const int src = (tid & 48) | (t & 15);     // the group's lane that holds row t
         // JB columns at a time
 #pragma unroll
         for (int j0 = 0; j0 < CPG; j0 += JB) {
-            double sd[JB], ns[JB];
+            // (the reflector is read again for the update: held over both
+            // loops it costs 20 registers that the columns need)
+            double u[RM];
 #pragma unroll
-            for (int j = 0; j < JB; ++j) sd[j] = ns[j] = 0.0;
+            for (int r = 0; r < RM; ++r) u[r] = svr[l16 + 16 * r];
+            double sd[JB], ns[JB], top[JB];
+#pragma unroll
+            for (int j = 0; j < JB; ++j) sd[j] = ns[j] = top[j] = 0.0;
 #pragma unroll
             for (int r = 0; r < RM; ++r) {
                 if (r < rt) continue;              // uniform: those slices hold R rows
 #pragma unroll
-                for (int j = 0; j < JB; ++j) sd[j] += u[r] * x[j0 + j][r];
+                for (int j = 0; j < JB; ++j) {
+                    if (r == rt) top[j] = __shfl(x[j0 + j][r], src);
+                    sd[j] = fma(u[r], x[j0 + j][r], sd[j]);
+                }
             }
 #pragma unroll
             for (int j = 0; j < JB; ++j) sd[j] = group16_sum(sd[j]);
 #pragma unroll
-            for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? c * sd[j] : 0.0;    // pivoted: rows kept
+            for (int j = 0; j < JB; ++j) sd[j] = act[j0 + j] ? beta * (sd[j] + top[j]) : 0.0;  // pivoted: rows kept
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int r = 0; r < RM; ++r) u[r] = svr[l16 + 16 * r];
 #pragma unroll
             for (int r = 0; r < RM; ++r) {
                 if (r < rt) continue;
+                // row t itself: u_t = 1
+                const double ur = r > rt ? u[r] : 16 * r == tl ? 1.0 : u[r];
 #pragma unroll
                 for (int j = 0; j < JB; ++j) {
-                    const double y = x[j0 + j][r] - sd[j] * u[r];
+                    const double y = fma(-sd[j], ur, x[j0 + j][r]);
                     x[j0 + j][r] = y;
-                    if (r > rt) ns[j] += y * y;
-                    else ns[j] += 16 * r > tl ? y * y : 0.0;
+                    const double z = r > rt || 16 * r > tl ? y : 0.0;
+                    ns[j] = fma(z, z, ns[j]);
                 }
             }
 #pragma unroll

@@ -37,3 +37,32 @@ def test_skeletons_and_projections(N, d, m, s, ell, tau):
             Pg, Po = g["P"][off:off + k * (n - k)].reshape(k, n - k), sk.proj(a)
             assert np.linalg.norm(Pg - Po) <= 1e-5 * max(1.0, np.linalg.norm(Po)), f"node {a}"
         off += min(s, min(ell, N - n_a), ncap) * ncap
+
+
+@pytest.mark.parametrize("N,d,leaf,s,ell", [(1000, 3, 63, 30, 60), (2000, 4, 125, 60, 90), (3600, 4, 225, 120, 148),
+                                            (1999, 12, 250, 63, 96)])
+def test_forms_agree_bit_for_bit(N, d, leaf, s, ell, monkeypatch):
+    """The register form and the gang (forced), and for more than 256 columns
+    allowed (a larger bound of the same tree's leaves) the streaming form, with
+    tau = 0 and a wide kernel: the last pivots are rounding, so one bit in any
+    step shows."""
+    import torch
+    from paper_1410_0260_amd import askit as A
+    print(f"\n[qr forms] N={N} d={d} leaf={leaf} s={s} l={ell}", flush=True)
+    X = torch.from_numpy(np.random.default_rng(N).standard_normal((N, d)).astype(np.float32)).cuda()
+    runs = []
+    for m, gang in ((leaf, ""), (leaf, "1"), (2 * leaf - 2, "0")):
+        if gang:
+            monkeypatch.setenv("ASKIT_QR_GANG", gang)
+        h = A.setup(X, A.default_params(leaf_size=m, kappa=8, max_skeleton=s, sample_rows=ell, id_tol=0.0,
+                                        bandwidth=2.0 * d ** 0.5, seed=3))
+        runs.append(h.structures())
+        h.close()
+    for g in runs[1:]:
+        assert np.array_equal(g["nodes"], runs[0]["nodes"])
+        for f in ("k", "S"):
+            assert np.array_equal(g[f], runs[0][f]), f
+        for a in range(1, len(g["k"])):
+            n = g["ncols"][a]
+            assert np.array_equal(g["colperm"][a, :n], runs[0]["colperm"][a, :n]), a
+        assert np.array_equal(g["P"], runs[0]["P"])
