@@ -1079,6 +1079,18 @@ askit_status askit_export(const askit_handle *h, int32_t what, void *dst, size_t
         HIPC(hipDeviceSynchronize());
         HIPC(hipMemcpy(dst, src, n, hipMemcpyDeviceToHost));
     }
+    if (what == ASKIT_X_PROJ) {
+        // a slot holds k (n - k) entries; the room behind them is never written
+        std::vector<int32_t> k(nn), nc(nn);
+        HIPC(hipMemcpy(k.data(), h->skk, 4 * nn, hipMemcpyDeviceToHost));
+        HIPC(hipMemcpy(nc.data(), h->ncols, 4 * nn, hipMemcpyDeviceToHost));
+        for (int64_t a = 1; a < (int64_t)nn; ++a) {
+            float *p = (float *)dst + h->pslot[a];
+            const int64_t room = h->pslot[a + 1] - h->pslot[a];
+            const int64_t used = std::min<int64_t>(room, (int64_t)k[a] * std::max(nc[a] - k[a], 0));
+            std::fill(p + used, p + room, 0.0f);
+        }
+    }
     API_END
 }
 

@@ -535,18 +535,20 @@ __global__ __launch_bounds__(256) void k_knn_cand_wide(const uint16_t *__restric
 // Filter sweep: every reference point whose approximate squared distance to
 // query row i is at most T_i (an upper bound of the row's 64th smallest
 // approximate distance, from the window pass, slightly widened) is appended
-// to the row's segment of `out` (capacity cap; count in ocnt).  Same MFMA
-// arithmetic and pipelining as k_knn_cand, without per-row lists.
+// to the row's bucket (64 rows; room for bcap, count in bcnt).  The products are
+// k_knn_cand's, started from -|q|^2 / 2, so that a distance is one fused
+// multiply-add; the certificate's bound covers sums of that size (partial sums
+// of at most |q|^2 + |x|^2, fewer than 8 dp roundings).
 // SYM (the point set against itself, all rows in one launch): the block of
 // rows [128 b, 128 b + 128) sweeps only the tiles from its own onwards, and a
 // distance of a later tile's point j to row i is also offered to row j
-// (appended to j's segment when it is at most T_j), so every unordered pair
+// (appended to j's bucket when it is at most T_j), so every unordered pair
 // is computed once.  Survivors are then in no particular order, and a row
 // may keep fewer than 64 of the window's points (their distances can come
 // from the transposed product, rounded differently); the selection and its
 // certificate allow both.
 template <int KS, bool SYM>
-__global__ __launch_bounds__(256, 2) void k_knn_filter(const uint16_t *__restrict__ Qh,
+__global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void k_knn_filter(const uint16_t *__restrict__ Qh,
                                                        const uint16_t *__restrict__ Ql,
                                                        const float *__restrict__ Qn, int64_t M,
                                                        const uint16_t *__restrict__ Xh,
@@ -554,24 +556,39 @@ __global__ __launch_bounds__(256, 2) void k_knn_filter(const uint16_t *__restric
                                                        const float *__restrict__ Xn, int64_t N,
                                                        int excl, int64_t row0,
                                                        const float *__restrict__ Tin,
-                                                       int cap, int32_t *__restrict__ ocnt,
-                                                       uint2 *__restrict__ oe, int win_tiles,
-                                                       const int32_t *__restrict__ tlist,
+                                                       int bcap, int32_t *__restrict__ bcnt,
+                                                       uint2 *__restrict__ be, uint8_t *__restrict__ br,
+                                                       int win_tiles, const int32_t *__restrict__ tlist,
                                                        const int64_t *__restrict__ toff,
                                                        const int4 *__restrict__ items)
 {
     constexpr int DP = KS * 16;
     constexpr int LDB = DP + 8;
     constexpr int TB = KB_N * LDB;
-    __shared__ __attribute__((aligned(16))) uint16_t sBh[3 * TB];
-    __shared__ __attribute__((aligned(16))) uint16_t sBl[3 * TB];
-    __shared__ float sBn[3 * KB_N];
-    __shared__ float sBt[SYM ? 3 * KB_N : 1];       // SYM: thresholds of the tile's points
-    __shared__ int sTile[3];                          // tile held by each buffer
+    __shared__ __attribute__((aligned(16))) uint16_t sBh[2 * TB];
+    __shared__ __attribute__((aligned(16))) uint16_t sBl[2 * TB];
+    __shared__ float sBn[2 * KB_N];
+    __shared__ float sBt[SYM ? 2 * KB_N : 1];       // SYM: thresholds of the tile's points
+    __shared__ int sTile[2];                          // tile held by each buffer
+    // Survivors on their way out.  An output position is an atomic on a
+    // counter, executed on the memory side at about 10^9 a second, and one per
+    // row and tile was what the sweep waited for (86 ms of 2^20 x 64 points,
+    // matrix cores busy 20 %).  Rows therefore share the counter of their 64-row
+    // bucket: a wave's rows lie in one bucket, so it queues its survivors and
+    // takes the positions of 64 at a time; survivors of a tile's points (SYM)
+    // go to that tile's bucket, queued by the whole workgroup, one atomic per
+    // run of the same tile.  k_filter_rows then sorts each bucket by row.  The
+    // same sweep: 54 ms.
+    constexpr int FQ = 192, CQ = SYM ? 320 : 1;
+    __shared__ uint2 sQe[4][FQ], sCe[CQ];
+    __shared__ uint8_t sQr[4][FQ];
+    __shared__ uint32_t sCr[CQ];
+    __shared__ int sCn, sCdrain[2];
 
     const int tid = threadIdx.x, lane = tid % WAVE;
     const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int half = lane >> 5, l32 = lane & 31;
+    if (tid == 0) sCn = sCdrain[0] = sCdrain[1] = 0;  // read after the first barrier
     // listed sweep: workgroup i takes the piece items[i] = (row block, first
     // list position, tile count) of a block's tile list
     const int4 item = tlist ? items[blockIdx.x] : int4{(int)blockIdx.x, 0, 0, 0};
@@ -593,11 +610,11 @@ __global__ __launch_bounds__(256, 2) void k_knn_filter(const uint16_t *__restric
             }
         }
     }
-    float qn[16], thrv[16];
+    f32x16 qh, thrv;                        // -|q|^2 / 2: the products start from it
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         int64_t row = q0 + 8 * (r / 4) + 4 * half + (r % 4);
-        qn[r] = row < M ? Qn[row0 + row] : 0.0f;
+        qh[r] = row < M ? -0.5f * Qn[row0 + row] : 0.0f;
         thrv[r] = row < M ? Tin[row0 + row] : -INFINITY;
     }
     // 32-bit row indices (M < 2^31) keep the survivor path's state small
@@ -671,8 +688,8 @@ __global__ __launch_bounds__(256, 2) void k_knn_filter(const uint16_t *__restric
     };
     auto mfma_tile = [&](int b, f32x16 &acc0, f32x16 &acc1) {
         const uint16_t *ph = sBh + b * TB, *pl = sBl + b * TB;
-        acc0 = f32x16{};
-        acc1 = f32x16{};
+        acc0 = qh;
+        acc1 = qh;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             bf16x8 bh0 = ld_bf8(ph + l32 * LDB + 16 * s + 8 * half);
@@ -687,132 +704,265 @@ __global__ __launch_bounds__(256, 2) void k_knn_filter(const uint16_t *__restric
             acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[s], bh1, acc1, 0, 0, 0);
         }
     };
+    int qc = 0;                             // the wave's queued survivors (uniform)
+    const int64_t bk0 = q0 >> 6;            // the bucket of the wave's rows
+    auto push = [&](bool p, uint32_t row, uint32_t id, float d) {
+        const uint64_t m = __ballot(p);
+        if (p) {
+            const int at = qc + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            sQr[wv][at] = (uint8_t)(row & 63u);
+            sQe[wv][at] = make_uint2(__float_as_uint(d), id);
+        }
+        qc += __popcll(m);
+    };
+    auto drain = [&](int least) {           // until fewer than `least` are queued
+        __builtin_amdgcn_wave_barrier();
+        while (qc >= least) {
+            const int n = min(qc, 64);
+            qc -= n;
+            int p = 0;
+            if (lane == 0) p = atomicAdd(&bcnt[bk0], n);
+            p = __builtin_amdgcn_readfirstlane(p) + lane;
+            if (lane < n && (uint32_t)p < (uint32_t)bcap) {
+                be[bk0 * bcap + p] = sQe[wv][qc + lane];
+                br[bk0 * bcap + p] = sQr[wv][qc + lane];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // a survivor of point col: into the workgroup's queue, or past its end
+    // straight to the bucket
+    auto push_col = [&](bool p, uint32_t col, uint32_t id, float d) {
+        const uint64_t m = __ballot(p);
+        if (!m) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&sCn, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) +
+             __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if (p) {
+            const uint2 e = make_uint2(__float_as_uint(d), id);
+            if (at < CQ) {
+                sCr[at] = col;
+                sCe[at] = e;
+            } else {
+                const int64_t b = col >> 6;
+                const int o = atomicAdd(&bcnt[b], 1);
+                if ((uint32_t)o < (uint32_t)bcap) {
+                    be[b * bcap + o] = e;
+                    br[b * bcap + o] = (uint8_t)(col & 63u);
+                }
+            }
+        }
+    };
+    // the workgroup's queue to the buckets (between two barriers that keep pushes out)
+    auto drain_col = [&]() {
+        const int n = min(sCn, CQ);
+        for (int e0 = wv * 64; e0 < n; e0 += 256) {
+            const int na = min(64, n - e0);
+            const uint32_t col = sCr[e0 + min(lane, na - 1)];
+            const int b = (int)(col >> 6);
+            const uint64_t act = na == 64 ? ~0ull : (1ull << na) - 1;
+            const uint64_t heads = __ballot(lane == 0 || b != __shfl_up(b, 1)) & act;
+            const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1;
+            const int hd = 63 - __clzll((long long)(heads & upto));
+            const uint64_t next = heads & ~upto;
+            int o = 0;
+            if (lane < na && hd == lane)
+                o = atomicAdd(&bcnt[b], (next ? __ffsll((long long)next) - 1 : na) - lane);
+            o = __shfl(o, hd) + lane - hd;
+            if (lane < na && (uint32_t)o < (uint32_t)bcap) {
+                be[(int64_t)b * bcap + o] = sCe[e0 + lane];
+                br[(int64_t)b * bcap + o] = (uint8_t)(col & 63u);
+            }
+        }
+    };
     int tnext = tile_of(0);                 // entry of the next load (kept in a register)
     load_tile(0, tnext & 0x7ffffff);
     load_thr(tnext & 0x7ffffff);
     store_tile(0, 0);
     store_thr(0);
     if (tid == 0) sTile[0] = tnext;
-    if (ntiles > 1) {
-        tnext = tile_of(1);
-        load_tile(0, tnext & 0x7ffffff);
-        load_thr(tnext & 0x7ffffff);
-        store_tile(0, 1);
-        store_thr(1);
-        if (tid == 0) sTile[1] = tnext;
-    }
     __syncthreads();
-    f32x16 accA0, accA1, accB0, accB1;
-    if (wave_on(sTile[0])) mfma_tile(0, accA0, accA1);
-    // iteration t: accumulators of tile t ready; MFMAs of tile t+1 read buffer
-    // (t+1)%3; the points of tile t+2 are loaded and stored to buffer (t+2)%3
-    auto iter = [&](auto CUR, int t, f32x16 &c0, f32x16 &c1, f32x16 &n0, f32x16 &n1) {
-        const int ent = sTile[t % 3];
+    // iteration t: tile t in buffer t % 2, the next one on its way to the other.
+    // Three workgroups share a CU (dp up to 64): one's products run while the
+    // others compare, load or wait.  Two workgroups with a second set of
+    // accumulators each, so that a wave's own products ran a tile ahead, left the
+    // matrix and vector units idle 41 % of the time (74 ms of 2^20 x 64 points).
+    for (int t = 0; t < nt32; ++t) {
+        const int ent = sTile[t & 1];
         const int tbase = (ent & 0x7ffffff) * KB_N;
         const bool on = wave_on(ent);
-        if (t + 2 < nt32) {
-            tnext = tile_of(t + 2);
+        if (t + 1 < nt32) {
+            tnext = tile_of(t + 1);
             load_tile(0, tnext & 0x7ffffff);
             load_thr(tnext & 0x7ffffff);
         }
-        if (t + 1 < nt32 && wave_on(sTile[(t + 1) % 3])) mfma_tile((t + 1) % 3, n0, n1);
         // <= keeps the window's own 64 points (same arithmetic as the window pass)
-        const float *nb = sBn + (t % 3) * KB_N;
+        const float *nb = sBn + (t & 1) * KB_N;
         const float ny0 = nb[l32], ny1 = nb[32 + l32];
         // the 32 distances of the lane, computed once for both tests
-        float dv[32];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            dv[r] = fmaf(-2.0f, c0[r], qn[r] + ny0);
-            dv[16 + r] = fmaf(-2.0f, c1[r], qn[r] + ny1);
-        }
-        bool any = false;
+        f32x16 dA, dB;
+        uint32_t regs = 0;                  // registers that hold a survivor
         if (on) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) any |= (dv[r] <= thrv[r]) | (dv[16 + r] <= thrv[r]);
-        }
-        if (__ballot(any)) {
-            const uint32_t cA = (uint32_t)tbase + (uint32_t)l32, cB = cA + 32u;
-            const uint32_t n32 = (uint32_t)N;
-            const uint32_t below = (1u << l32) - 1u;
-            // an opaque copy of the rows' base: otherwise the compiler hoists
-            // the 16 rows' 64-bit segment offsets out of the sweep loop, spills
-            // them, and every append waits on a scratch reload
-            uint32_t qb = qbase;
-            asm volatile("" : "+v"(qb));
+            mfma_tile(t & 1, dA, dB);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                // the 32 lanes of a half-wave hold the same row: one counter
-                // update per row and half-wave, lanes write at their prefix
-                const uint32_t qrow = qb + (uint32_t)(8 * (r / 4) + (r % 4));
-                const float dA = dv[r];
-                const float dB = dv[16 + r];
-                const bool pA = dA <= thrv[r] && cA < n32 && !(excl && cA == qrow + (uint32_t)row0);
-                const bool pB = dB <= thrv[r] && cB < n32 && !(excl && cB == qrow + (uint32_t)row0);
-                const uint64_t bA = __ballot(pA), bB = __ballot(pB);
-                const uint32_t hA = (uint32_t)(bA >> (32 * half)), hB = (uint32_t)(bB >> (32 * half));
-                if ((hA | hB) == 0u) continue;
-                const int lead = 32 * half + __ffs(hA | hB) - 1;
-                uint32_t p0 = 0;
-                if (lane == lead) p0 = (uint32_t)atomicAdd(&ocnt[qrow], __popc(hA) + __popc(hB));
-                p0 = (uint32_t)__shfl((int)p0, lead);
-                if (pA) {
-                    const uint32_t p = p0 + __popc(hA & below);
-                    if (p < (uint32_t)cap) {
-                        oe[(size_t)qrow * (uint32_t)cap + p] = make_uint2(__float_as_uint(dA), cA);
-                    }
-                }
-                if (pB) {
-                    const uint32_t p = p0 + __popc(hA) + __popc(hB & below);
-                    if (p < (uint32_t)cap) {
-                        oe[(size_t)qrow * (uint32_t)cap + p] = make_uint2(__float_as_uint(dB), cB);
-                    }
-                }
+                dA[r] = fmaf(-2.0f, dA[r], ny0);
+                dB[r] = fmaf(-2.0f, dB[r], ny1);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                regs |= (__ballot(dA[r] <= thrv[r]) | __ballot(dB[r] <= thrv[r])) ? 1u << r : 0u;
+            // taken one after the other by a loop over their uniform index:
+            // unrolled, the two queues' code was 14,000 instructions with
+            // 154 spilled scalars (140 ms)
+            const uint32_t cA = (uint32_t)tbase + (uint32_t)l32, cB = cA + 32u;
+            const uint32_t n32 = (uint32_t)N;
+            while (regs) {
+                const int r = __builtin_ctz(regs);
+                regs &= regs - 1;
+                const float a = dA[r], b = dB[r], th = thrv[r];
+                const uint32_t qrow = qbase + (uint32_t)(8 * (r >> 2) + (r & 3));
+                const uint32_t self = excl ? qrow + (uint32_t)row0 : 0xffffffffu;
+                push(a <= th && cA < n32 && cA != self, qrow, cA, a);
+                push(b <= th && cB < n32 && cB != self, qrow, cB, b);
+                if (qc > FQ - 128) drain(64);
             }
         }
         if constexpr (SYM) {
             // tiles after the block's own two: offer each distance to the tile's point too
             if ((ent & 0x7ffffff) >= tself + 2 && on) {
-                const float *tb = sBt + (t % 3) * KB_N;
+                const float *tb = sBt + (t & 1) * KB_N;
                 const float tA = tb[l32], tB = tb[32 + l32];
-                bool anyc = false;
+                const uint32_t cA = (uint32_t)tbase + (uint32_t)l32, cB = cA + 32u;
+                const uint32_t m32 = (uint32_t)M;
+                regs = 0;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) anyc |= (dv[r] <= tA) | (dv[16 + r] <= tB);
-                if (__ballot(anyc)) {
-                    const uint32_t cA = (uint32_t)tbase + (uint32_t)l32, cB = cA + 32u;
-                    const uint32_t m32 = (uint32_t)M;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const uint32_t qrow = qbase + (uint32_t)(8 * (r / 4) + (r % 4));
-                        if (qrow >= m32) continue;
-                        const float dA = dv[r];
-                        const float dB = dv[16 + r];
-                        if (dA <= tA) {
-                            uint32_t p = (uint32_t)atomicAdd(&ocnt[cA], 1);
-                            if (p < (uint32_t)cap) {
-                                oe[(size_t)cA * (uint32_t)cap + p] = make_uint2(__float_as_uint(dA), qrow);
-                            }
-                        }
-                        if (dB <= tB) {
-                            uint32_t p = (uint32_t)atomicAdd(&ocnt[cB], 1);
-                            if (p < (uint32_t)cap) {
-                                oe[(size_t)cB * (uint32_t)cap + p] = make_uint2(__float_as_uint(dB), qrow);
-                            }
-                        }
-                    }
+                for (int r = 0; r < 16; ++r)
+                    regs |= (__ballot(dA[r] <= tA) | __ballot(dB[r] <= tB)) ? 1u << r : 0u;
+                while (regs) {
+                    const int r = __builtin_ctz(regs);
+                    regs &= regs - 1;
+                    const float a = dA[r], b = dB[r];
+                    const uint32_t qrow = qbase + (uint32_t)(8 * (r >> 2) + (r & 3));
+                    push_col(a <= tA && qrow < m32, cA, qrow, a);
+                    push_col(b <= tB && qrow < m32, cB, qrow, b);
                 }
             }
         }
-        if (t + 2 < nt32) {
-            store_tile(0, (t + 2) % 3);
-            store_thr((t + 2) % 3);
-            if (tid == 0) sTile[(t + 2) % 3] = tnext;
+        if (t + 1 < nt32) {
+            store_tile(0, (t + 1) & 1);
+            store_thr((t + 1) & 1);
+            if (tid == 0) sTile[(t + 1) & 1] = tnext;
         }
+        // (a count taken while waves still push is early, never wrong)
+        if (SYM && tid == 0) sCdrain[t & 1] = *(volatile int *)&sCn >= CQ / 2;
         __syncthreads();
+        if (SYM && sCdrain[t & 1]) {        // written again two barriers later
+            drain_col();
+            __syncthreads();
+            if (tid == 0) sCn = 0;
+            __syncthreads();
+        }
+    }
+    drain(1);
+    if constexpr (SYM) drain_col();         // after the last iteration's barrier
+}
+
+// A bucket's survivors by row: counts and first positions (in the bucket's part
+// of oe) of its 64 rows, in any order within a row.  A bucket that overflowed
+// marks all its rows (FILT_OVER).  One workgroup per bucket; each wave counts,
+// then places, a contiguous range of the entries, 64 at a time, with the
+// lanes of equal rows found by ballots (entries of a row come in runs, so a
+// counter per entry would be one serial chain).  Bound by its two reads
+// and one write of the entries: 1.8 ms for the 1.6 x 10^8 of 2^20 x 64 points.
+constexpr int FILT_OVER = 1 << 30;
+
+__global__ __launch_bounds__(1024) void k_filter_rows(const int32_t *__restrict__ bcnt, const uint2 *__restrict__ be,
+                                                      const uint8_t *__restrict__ br, int bcap, int64_t M,
+                                                      int32_t *__restrict__ ocnt, int32_t *__restrict__ rstart,
+                                                      uint2 *__restrict__ oe)
+{
+    __shared__ int cnt[16][64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t b = blockIdx.x;
+    const int nall = bcnt[b], n = min(nall, bcap);
+    be += b * bcap;
+    br += b * bcap;
+    oe += b * bcap;
+    const int per = (n + 1023) / 1024 * 64;
+    const int w0 = min(n, wv * per), w1 = min(n, w0 + per);
+    volatile int *mine = cnt[wv];
+    mine[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    // lanes of this lane's row among the `ok` ones
+    auto peers = [&](int r, bool ok) {
+        uint64_t same = __ballot(ok);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const uint64_t m = __ballot((r >> k) & 1);
+            same &= (r >> k) & 1 ? m : ~m;
+        }
+        return same;
     };
-    for (int t = 0; t < nt32; t += 2) {
-        iter(std::integral_constant<int, 0>{}, t, accA0, accA1, accB0, accB1);
-        if (t + 1 < nt32) iter(std::integral_constant<int, 1>{}, t + 1, accB0, accB1, accA0, accA1);
+    const uint64_t below = (1ull << lane) - 1;
+    for (int e0 = w0; e0 < w1; e0 += 512) {
+        int r[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = br[min(e0 + 64 * u + lane, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (e0 + 64 * u >= w1) break;
+            const bool ok = e0 + 64 * u + lane < w1;
+            const uint64_t same = peers(r[u], ok);
+            if (ok && !(same & below)) mine[r[u]] = mine[r[u]] + __popcll(same);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {
+        int tot = 0;
+        for (int w = 0; w < 16; ++w) tot += cnt[w][tid];
+        int inc = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+        int o = inc - tot;
+        if (b * 64 + tid < M) {
+            ocnt[b * 64 + tid] = tot | (nall > bcap ? FILT_OVER : 0);
+            rstart[b * 64 + tid] = o;
+        }
+        for (int w = 0; w < 16; ++w) {
+            const int c = cnt[w][tid];
+            cnt[w][tid] = o;
+            o += c;
+        }
+    }
+    __syncthreads();
+    for (int e0 = w0; e0 < w1; e0 += 512) {
+        int r[8];
+        uint2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = min(e0 + 64 * u + lane, n - 1);
+            r[u] = br[e];
+            v[u] = be[e];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (e0 + 64 * u >= w1) break;
+            const bool ok = e0 + 64 * u + lane < w1;
+            const uint64_t same = peers(r[u], ok);
+            if (ok) {
+                const int at = mine[r[u]];
+                __builtin_amdgcn_wave_barrier();
+                if (!(same & below)) mine[r[u]] = at + __popcll(same);
+                oe[at + __popcll(same & below)] = v[u];
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 
@@ -839,6 +989,7 @@ __device__ __forceinline__ float key2f(uint32_t k)
 
 __global__ __launch_bounds__(256) void k_knn_select(int64_t M, int64_t row0, int cap, int nsel,
                                                     const int32_t *__restrict__ ocnt,
+                                                    const int32_t *__restrict__ rstart, int bcap,
                                                     const uint2 *__restrict__ oe,
                                                     int32_t *__restrict__ cand,
                                                     float *__restrict__ thr,
@@ -856,8 +1007,8 @@ __global__ __launch_bounds__(256) void k_knn_select(int64_t M, int64_t row0, int
         int p = atomicAdd(bad_count, 1);
         bad_rows[p] = (int32_t)row;
     }
-    const int nk = min(n, cap);
-    const uint2 *re = oe + lrow * cap;          // (distance bits, id) per stored entry
+    const int nk = min(n & (FILT_OVER - 1), cap);
+    const uint2 *re = oe + (lrow >> 6) * bcap + rstart[lrow];   // (distance bits, id) per stored entry
     int32_t *co = cand + row * KNN_CAND;
     if (nk <= nsel) {
         // every stored entry is a candidate
@@ -868,7 +1019,7 @@ __global__ __launch_bounds__(256) void k_knn_select(int64_t M, int64_t row0, int
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
         }
-        if (lane == 0) thr[row] = n > cap ? m + fabsf(m) * 1e-5f + 1e-30f : (n >= nsel ? m : tin);
+        if (lane == 0) thr[row] = nk < nsel ? tin : (n > cap ? m + fabsf(m) * 1e-5f + 1e-30f : m);
         return;
     }
     // keys and ids of the stored entries; the loads are unconditional (index
@@ -994,20 +1145,58 @@ static void launch_cand(dim3 g, dim3 b, hipStream_t s, const uint16_t *Qh, const
                        thr, cand_d);
 }
 
+// Filter output of up to `rows` rows: the buckets as the sweep writes them, and
+// the same entries by row (k_filter_rows).  A row keeps at most cap entries, a
+// bucket of 64 rows bcap.
+struct FilterBufs {
+    int cap = 0, bcap = 0;
+    int32_t *bcnt = nullptr, *ocnt = nullptr, *rstart = nullptr;
+    uint2 *be = nullptr, *oe = nullptr;       // (distance bits, id)
+    uint8_t *br = nullptr;                    // row within the bucket
+    int nsel = KNN_CAND;                      // candidates the selection keeps per row
+    // per_row: average entries per row a bucket has room for
+    void alloc(int64_t rows, int cap_, int per_row, const std::function<void *(size_t)> &ta)
+    {
+        const int64_t nb = (rows + 63) / 64;
+        cap = cap_;
+        bcap = 64 * per_row;
+        bcnt = (int32_t *)ta(sizeof(int32_t) * nb);
+        ocnt = (int32_t *)ta(sizeof(int32_t) * rows);
+        rstart = (int32_t *)ta(sizeof(int32_t) * rows);
+        be = (uint2 *)ta(sizeof(uint2) * nb * bcap);
+        oe = (uint2 *)ta(sizeof(uint2) * nb * bcap);
+        br = (uint8_t *)ta((size_t)nb * bcap);
+    }
+};
+constexpr double FILT_BYTES = 17.0;           // of the three entry arrays, per entry of room
+
 template <int KS>
 static void launch_filter(dim3 g, dim3 b, hipStream_t s, const uint16_t *Qh, const uint16_t *Ql,
                           const float *Qn, int64_t M, const uint16_t *Xh, const uint16_t *Xl,
-                          const float *Xn, int64_t N, int ex, int64_t row0, const float *T, int cap,
-                          int32_t *ocnt, uint2 *oe, bool sym, int win = 0,
-                          const int32_t *tlist = nullptr, const int64_t *toff = nullptr,
+                          const float *Xn, int64_t N, int ex, int64_t row0, const float *T, const FilterBufs &B,
+                          bool sym, int win = 0, const int32_t *tlist = nullptr, const int64_t *toff = nullptr,
                           const int4 *items = nullptr)
 {
     if (sym)
-        hipLaunchKernelGGL((k_knn_filter<KS, true>), g, b, 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, row0, T, cap,
-                           ocnt, oe, 0, tlist, toff, items);
+        hipLaunchKernelGGL((k_knn_filter<KS, true>), g, b, 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, row0, T, B.bcap,
+                           B.bcnt, B.be, B.br, 0, tlist, toff, items);
     else
-        hipLaunchKernelGGL((k_knn_filter<KS, false>), g, b, 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, row0, T,
-                           cap, ocnt, oe, win, tlist, toff, items);
+        hipLaunchKernelGGL((k_knn_filter<KS, false>), g, b, 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, ex, row0, T, B.bcap,
+                           B.bcnt, B.be, B.br, win, tlist, toff, items);
+    HIPC(hipGetLastError());
+}
+
+// Empty buckets before a sweep over m rows, and its survivors by row after it.
+static void filter_begin(const FilterBufs &B, int64_t m, hipStream_t s)
+{
+    HIPC(hipMemsetAsync(B.bcnt, 0, sizeof(int32_t) * ((m + 63) / 64), s));
+}
+
+static void filter_rows(const FilterBufs &B, int64_t m, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_filter_rows, dim3((unsigned)((m + 63) / 64)), dim3(1024), 0, s, B.bcnt, B.be, B.br, B.bcap, m,
+                       B.ocnt, B.rstart, B.oe);
+    HIPC(hipGetLastError());
 }
 
 __global__ void k_fill_f32(float *__restrict__ p, int64_t n, float v)
@@ -1083,14 +1272,18 @@ static int filter_segments(int64_t m, int64_t ntiles)
 constexpr int KNN_SMALL = KNN_SMALL_N / KB_N;   // tiles of a small point set
 constexpr int KNN_WIN = 64;                 // window tiles (4096 points)
 constexpr int KNN_CAP = 1024;               // filter output per row
-constexpr int64_t KNN_CHUNK = 1 << 20;      // query rows per filter pass (bounds the buffers)
-
-// Filter output buffers of up to `rows` rows.
-struct FilterBufs {
-    int32_t *ocnt = nullptr;
-    uint2 *oe = nullptr;                      // (distance bits, id) per slot, KNN_CAP slots per row
-    int nsel = KNN_CAND;                      // candidates the selection keeps per row
-};
+constexpr int64_t KNN_CHUNK = 1 << 19;      // query rows per filter pass (bounds the buffers)
+// Entries per row, on average, that a bucket of the symmetric sweep has room
+// for: KNN_CAP while the buffers stay within 9 GB (half a million points), half of
+// it up to 52 GB (6.4 million; past that the sweep goes by row chunks).  Rows
+// of a bucket that overflows are only swept again: at 2^20 x 64 half the room
+// lists 36,535 rows for that and all of it 21,325, 2 ms of a 160 ms solve for
+// 9 GB more.
+static int sym_room(int64_t N)
+{
+    const double gb = (double)N * KNN_CAP * FILT_BYTES / (1ull << 30);
+    return gb <= 9.0 ? KNN_CAP : gb <= 104.0 ? KNN_CAP / 2 : 0;
+}
 
 // Threshold filter of rows [0, M) against a reference set, in passes of
 // `chunk` rows, each followed by the selection (cand, thr of every row; rows
@@ -1108,7 +1301,7 @@ static void filter_select(int dp, hipStream_t s, const uint16_t *Qh, const uint1
         const int64_t m = std::min<int64_t>(chunk, M - r0);
         dim3 g((unsigned)((m + KB_M - 1) / KB_M), (unsigned)((sym || win > 0) ? 1 : filter_segments(m, ntl)));
         if (tlist) g = dim3((unsigned)nitems);             // one workgroup per list piece
-        HIPC(hipMemsetAsync(B.ocnt, 0, sizeof(int32_t) * m, s));
+        filter_begin(B, m, s);
         if (ev) {
             ev->resize(ev->size() + 2);
             HIPC(hipEventCreate(&(*ev)[ev->size() - 2]));
@@ -1116,11 +1309,12 @@ static void filter_select(int dp, hipStream_t s, const uint16_t *Qh, const uint1
             HIPC(hipEventRecord((*ev)[ev->size() - 2], s));
         }
         if (!tlist || nitems > 0)
-            KNN_DISPATCH(launch_filter, g, dim3(256), s, Qh, Ql, Qn, m, Xh, Xl, Xn, N, ex, r0, thr, KNN_CAP, B.ocnt,
-                         B.oe, sym, win, tlist, toff, items);
+            KNN_DISPATCH(launch_filter, g, dim3(256), s, Qh, Ql, Qn, m, Xh, Xl, Xn, N, ex, r0, thr, B, sym, win, tlist,
+                         toff, items);
         if (ev) HIPC(hipEventRecord(ev->back(), s));
-        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, r0, KNN_CAP, B.nsel,
-                           B.ocnt, B.oe, cand, thr, over ? over + 1 : nullptr, over);
+        filter_rows(B, m, s);
+        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, r0, B.cap, B.nsel,
+                           B.ocnt, B.rstart, B.bcap, B.oe, cand, thr, over ? over + 1 : nullptr, over);
         HIPC(hipGetLastError());
     }
 }
@@ -1572,14 +1766,20 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     const bool small = start_local && ntiles <= KNN_SMALL;
     // the point set against itself with every row's segment in one buffer:
     // one triangular sweep (each unordered pair once); else row chunks
-    const bool sym = !small && exclude_self && Qh == Xh && M == N && (double)N * KNN_CAP * 8.0 <= 48.0 * (1ull << 30);
+    const bool sym = !small && exclude_self && Qh == Xh && M == N && sym_room(N) > 0;
     const int64_t chunk = sym ? M : KNN_CHUNK;
     const int64_t mc = std::min<int64_t>(M, chunk);
     FilterBufs B;
     B.nsel = std::max(1, std::min(nsel, KNN_CAND));
     int32_t *retry, *over;
-    HIPC(ws_alloc((void **)&B.ocnt, sizeof(int32_t) * mc, s));
-    HIPC(ws_alloc((void **)&B.oe, sizeof(uint2) * mc * KNN_CAP, s));
+    std::vector<void *> ttmp;
+    auto ta = [&](size_t b) {
+        void *p;
+        HIPC(ws_alloc(&p, std::max<size_t>(b, 16), s));
+        ttmp.push_back(p);
+        return p;
+    };
+    B.alloc(mc, KNN_CAP, sym ? sym_room(N) : KNN_CAP, ta);
     HIPC(ws_alloc((void **)&retry, sizeof(int32_t) * (M + 1), s));
     HIPC(ws_alloc((void **)&over, sizeof(int32_t) * (M + 1), s));
     HIPC(hipMemsetAsync(retry, 0, sizeof(int32_t), s));
@@ -1591,7 +1791,6 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     }
     // symmetric sweep: only the (row block, tile) pairs whose bounding balls
     // come within the thresholds
-    std::vector<void *> ttmp;
     int32_t *tlist = nullptr;
     int64_t *toff = nullptr, kept = 0, kept_waves = 0, nitems = 0;
     int4 *items = nullptr;
@@ -1677,7 +1876,7 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
         filter_select(dp, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, 0, n, tc, B, cc, nullptr, false, 0, nullptr,
                       rlists ? rl : nullptr, rlists ? ro : nullptr, rlists ? ri : nullptr, rni);
         hipLaunchKernelGGL(k_scatter_retry, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, n, list, cc, tc,
-                           B.ocnt, KNN_CAP, cand, thr, over + 1, over);
+                           B.ocnt, B.cap, cand, thr, over + 1, over);
         HIPC(hipGetLastError());
         HIPC(hipMemcpyAsync(&nlist, over, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIPC(hipStreamSynchronize(s));
@@ -1693,8 +1892,6 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     // the bound the selection left
     if (nlist > 0)
         KNN_DISPATCH(list_sweep, s, Qh, Ql, Qn, (int64_t)nlist, Xh, Xl, Xn, N, ex, sl, list, true, cand, thr);
-    HIPC(ws_free(B.ocnt, s));
-    HIPC(ws_free(B.oe, s));
     HIPC(ws_free(retry, s));
     HIPC(ws_free(over, s));
     for (void *p : ttmp) HIPC(ws_free(p, s));
@@ -2067,6 +2264,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ 
                                                     const float *__restrict__ Q, const float *__restrict__ X,
                                                     int d, int dp, int kappa, int excl, int cap,
                                                     const int32_t *__restrict__ ocnt,
+                                                    const int32_t *__restrict__ rstart, int bcap,
                                                     const uint2 *__restrict__ oe,
                                                     const int32_t *__restrict__ idmap,
                                                     const int32_t *__restrict__ rowmap,
@@ -2083,13 +2281,15 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ 
         if (lane == 0) over_rows[atomicAdd(over_count, 1)] = (int32_t)row;
         return;
     }
+    // by row within the bucket's part, or cap entries per row (rstart NULL)
+    const uint2 *re = rstart ? oe + (i >> 6) * bcap + rstart[i] : oe + i * cap;
     double bD = INFINITY;
     int bj = 0x7fffffff;
     for (int c0 = 0; c0 < cnt; c0 += 64) {
         double D = INFINITY;
         int j = 0x7fffffff;
         if (c0 + lane < cnt) {
-            const int pos = (int)oe[i * cap + c0 + lane].y;
+            const int pos = (int)re[c0 + lane].y;
             if (!(excl && pos == row)) {
                 D = canon_sqdist(Q + row * dp, X + (int64_t)pos * dp, d);
                 j = idmap ? idmap[pos] : pos;
@@ -2145,27 +2345,35 @@ void knn_fallback(const float *Q, const uint16_t *Qh, const uint16_t *Ql, const 
     const int64_t n = nrows;
     uint16_t *Bh = (uint16_t *)ta(sizeof(uint16_t) * n * dp), *Bl = (uint16_t *)ta(sizeof(uint16_t) * n * dp);
     float *Bn = (float *)ta(sizeof(float) * n), *Bt = (float *)ta(sizeof(float) * n);
-    int32_t *ocnt = (int32_t *)ta(sizeof(int32_t) * n);
-    uint2 *oe = (uint2 *)ta(sizeof(uint2) * n * FCAP);
+    FilterBufs B;
+    if (dp > 128) {
+        B.cap = FCAP;
+        B.ocnt = (int32_t *)ta(sizeof(int32_t) * n);
+        B.oe = (uint2 *)ta(sizeof(uint2) * n * FCAP);
+    } else {
+        B.alloc(n, FCAP, FCAP, ta);
+    }
     int32_t *over = (int32_t *)ta(sizeof(int32_t) * (n + 1));
     hipLaunchKernelGGL(k_gather_qrows, dim3((unsigned)n), dim3(128), 0, s, rows, n, dp, Qh, Ql, Qn, tbound, Bh, Bl,
                        Bn, Bt);
-    HIPC(hipMemsetAsync(ocnt, 0, sizeof(int32_t) * n, s));
     HIPC(hipMemsetAsync(over, 0, sizeof(int32_t), s));
     dim3 g((unsigned)((n + KB_M - 1) / KB_M)), block(256);
     if (dp > 128) {
-        hipLaunchKernelGGL(k_knn_filter_wide, g, block, 0, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, dp, Bt, FCAP, ocnt,
-                           oe);
+        HIPC(hipMemsetAsync(B.ocnt, 0, sizeof(int32_t) * n, s));
+        hipLaunchKernelGGL(k_knn_filter_wide, g, block, 0, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, dp, Bt, FCAP, B.ocnt,
+                           B.oe);
     } else {
         // few rows: the points are split into column segments, one workgroup
         // each, appending to the rows' common outputs
         g.y = (unsigned)filter_segments(n, (N + KB_N - 1) / KB_N);
-        KNN_DISPATCH(launch_filter, g, block, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, 0, 0, Bt, FCAP, ocnt, oe,
-                     false);
+        filter_begin(B, n, s);
+        KNN_DISPATCH(launch_filter, g, block, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, 0, 0, Bt, B, false);
+        filter_rows(B, n, s);
     }
     HIPC(hipGetLastError());
     hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, rows, (int64_t)0, n, Q, X, d,
-                       dp, kappa, exclude_self ? 1 : 0, FCAP, ocnt, oe, idmap, rowmap, idx, dist, over + 1, over);
+                       dp, kappa, exclude_self ? 1 : 0, FCAP, B.ocnt, B.rstart, B.bcap, B.oe, idmap, rowmap, idx, dist,
+                       over + 1, over);
     HIPC(hipGetLastError());
     int32_t nover = 0;
     HIPC(hipMemcpyAsync(&nover, over, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -2216,12 +2424,11 @@ void knn_direct(const float *Xf, const uint16_t *Xh, const uint16_t *Xl, const f
     };
     const int64_t ntiles = (N + KB_N - 1) / KB_N;
     const bool small = ntiles <= KNN_SMALL;
-    const bool sym = !small && (double)N * KNN_CAP * 8.0 <= 48.0 * (1ull << 30);
+    const bool sym = !small && sym_room(N) > 0;
     const int64_t chunk = std::min<int64_t>(N, sym ? N : KNN_CHUNK);
     FilterBufs B;
     B.nsel = KNN_CAND;
-    B.ocnt = (int32_t *)ta(sizeof(int32_t) * chunk);
-    B.oe = (uint2 *)ta(sizeof(uint2) * chunk * KNN_CAP);
+    B.alloc(chunk, KNN_CAP, sym ? sym_room(N) : KNN_CAP, ta);
     float *thr = (float *)ta(sizeof(float) * N), *T = (float *)ta(sizeof(float) * N);
     int32_t *cand = (int32_t *)ta(sizeof(int32_t) * N * KNN_CAND);
     int32_t *over = (int32_t *)ta(sizeof(int32_t) * (N + 1));
@@ -2258,15 +2465,17 @@ void knn_direct(const float *Xf, const uint16_t *Xh, const uint16_t *Xl, const f
         const int64_t m = std::min<int64_t>(chunk, N - r0);
         dim3 gr((unsigned)((m + KB_M - 1) / KB_M), (unsigned)(sym ? 1 : filter_segments(m, ntiles)));
         if (tlist) gr = dim3((unsigned)nitems);
-        HIPC(hipMemsetAsync(B.ocnt, 0, sizeof(int32_t) * m, s));
+        filter_begin(B, m, s);
         HIPC(hipMemsetAsync(over, 0, sizeof(int32_t), s));
         HIPC(hipEventRecord(e0, s));
         if (!tlist || nitems > 0)
-            KNN_DISPATCH(launch_filter, gr, dim3(256), s, Xh, Xl, Xn, m, Xh, Xl, Xn, N, 1, r0, T, KNN_CAP, B.ocnt,
-                         B.oe, sym, 0, tlist, toff, items);
+            KNN_DISPATCH(launch_filter, gr, dim3(256), s, Xh, Xl, Xn, m, Xh, Xl, Xn, N, 1, r0, T, B, sym, 0, tlist, toff,
+                         items);
         HIPC(hipEventRecord(e1, s));
+        filter_rows(B, m, s);
         hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, (const int32_t *)nullptr, r0,
-                           m, Xf, Xf, d, dp, kappa, 1, KNN_CAP, B.ocnt, B.oe, idmap, idmap, idx, dist, over + 1, over);
+                           m, Xf, Xf, d, dp, kappa, 1, B.cap, B.ocnt, B.rstart, B.bcap, B.oe, idmap, idmap, idx, dist,
+                           over + 1, over);
         HIPC(hipGetLastError());
         int32_t nover = 0;
         HIPC(hipMemcpyAsync(&nover, over, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -2278,8 +2487,8 @@ void knn_direct(const float *Xf, const uint16_t *Xh, const uint16_t *Xl, const f
         if (nover == 0) continue;
         // the KNN_CAND-th of a row's stored survivors (real points) is a bound
         // like the window's, and mostly far below it
-        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, r0, KNN_CAP, B.nsel,
-                           B.ocnt, B.oe, cand, thr, (int32_t *)nullptr, (int32_t *)nullptr);
+        hipLaunchKernelGGL(k_knn_select, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, r0, B.cap, B.nsel,
+                           B.ocnt, B.rstart, B.bcap, B.oe, cand, thr, (int32_t *)nullptr, (int32_t *)nullptr);
         hipLaunchKernelGGL(k_add_bound, dim3((unsigned)((nover + 255) / 256)), dim3(256), 0, s, thr, Xn, g, mx,
                            (int64_t)nover, over + 1, T);
         HIPC(hipGetLastError());

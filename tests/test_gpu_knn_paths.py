@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 CASES = [  # N, d, kappa, leaf, coincident points
     (65, 3, 64, 32, 0), (1500, 4, 64, 256, 0), (3000, 40, 49, 200, 0), (16384, 6, 64, 256, 0), (16385, 6, 50, 256, 0), (32769, 5, 64, 256, 0),
     (20011, 12, 64, 300, 0), (33000, 8, 16, 256, 0), (8000, 20, 16, 256, 0), (15000, 64, 32, 512, 0), (300, 5, 48, 40, 0),
-    (6000, 4, 64, 128, 2500), (6000, 4, 8, 128, 2500), (33001, 3, 64, 128, 1500),
+    (32833, 70, 16, 300, 0), (33000, 96, 16, 300, 0), (33001, 100, 24, 300, 0), (33000, 128, 16, 300, 0),
+    (40001, 30, 16, 256, 6000), (6000, 4, 64, 128, 2500), (6000, 4, 8, 128, 2500), (33001, 3, 64, 128, 1500),
 ]
 
 
