@@ -869,6 +869,196 @@ __global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void k_knn_filter(const uint1
     if constexpr (SYM) drain_col();         // after the last iteration's barrier
 }
 
+// The filter for more than 128 dimensions, with the same outputs.  A workgroup
+// takes 128 x 128 pairs at a time, a wave 64 x 64 of them in four accumulators
+// (each fragment read from LDS serves two products), both operands staged in LDS
+// WF_K dimensions at a time while the next are loaded into registers.
+// Columns: the win_tiles tiles (64 points) around the rows, or part blockIdx.y of the
+// sweep (SYM: of the blocks from the row block's own on, WF_PIECE per part, a
+// distance being offered to its column too).  Bound by the LDS reads of the
+// fragments and their latency; a wave's rows, and its columns, lie in one
+// bucket, so its queue is drained after each 64 x 64.  50,001 x 1,000: 73 ms with
+// per-row lists over 128 x 64 pairs, the query fragments read from memory for
+// every tile and 391 workgroups for the chip; 17 ms here, windows included.
+constexpr int WF_K = 32, WF_LD = WF_K + 8, WF_PIECE = 16;
+
+template <bool SYM>
+__global__ __launch_bounds__(256, 2) void k_knn_filter_wide(
+    const uint16_t *__restrict__ Qh, const uint16_t *__restrict__ Ql, const float *__restrict__ Qn, int64_t M,
+    const uint16_t *__restrict__ Xh, const uint16_t *__restrict__ Xl, const float *__restrict__ Xn, int64_t N, int dp,
+    int excl, int64_t row0, const float *__restrict__ Tin, int bcap, int32_t *__restrict__ bcnt,
+    uint2 *__restrict__ be, uint8_t *__restrict__ br, int win_tiles)
+{
+    constexpr int FQ = 192;
+    __shared__ __attribute__((aligned(16))) uint16_t sm[4][128 * WF_LD];   // rows high, low; columns high, low
+    __shared__ __attribute__((aligned(16))) float sQn[128], sThr[128];
+    __shared__ uint2 sQe[4][FQ];
+    __shared__ uint8_t sQr[4][FQ];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wv >> 1, wc = wv & 1, half = lane >> 5, l32 = lane & 31;
+    const int64_t bx = blockIdx.x, q0 = bx * 128;
+    // columns [cb, ce) of this workgroup
+    int64_t cb = 0, ce = N;
+    if (SYM) {
+        cb = max((int64_t)blockIdx.y * WF_PIECE, bx) * 128;
+        ce = min(N, ((int64_t)blockIdx.y + 1) * WF_PIECE * 128);
+    } else if (win_tiles > 0) {
+        const int64_t nt = (N + KB_N - 1) / KB_N;
+        if (win_tiles < nt) {
+            const int64_t c = (row0 + q0) / KB_N + (KB_M / KB_N) / 2 - win_tiles / 2;
+            const int64_t t0 = c < 0 ? 0 : (c + win_tiles > nt ? nt - win_tiles : c);
+            cb = t0 * KB_N;
+            ce = min(N, (t0 + win_tiles) * KB_N);
+        }
+    } else if (gridDim.y > 1) {
+        const int64_t nt = (N + 127) / 128, per = (nt + gridDim.y - 1) / gridDim.y;
+        cb = blockIdx.y * per * 128;
+        ce = min(N, cb + per * 128);
+    }
+    if (cb >= ce) return;
+    if (tid < 128) {
+        const bool ok = q0 + tid < M;
+        sQn[tid] = ok ? Qn[row0 + q0 + tid] : 0.0f;
+        sThr[tid] = ok ? Tin[row0 + q0 + tid] : -INFINITY;
+    }
+    int qc = 0;                             // the wave's queued survivors (uniform)
+    auto push = [&](bool p, uint32_t row, uint32_t id, float d) {
+        const uint64_t m = __ballot(p);
+        if (p) {
+            const int at = qc + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            sQr[wv][at] = (uint8_t)(row & 63u);
+            sQe[wv][at] = make_uint2(__float_as_uint(d), id);
+        }
+        qc += __popcll(m);
+    };
+    auto drain = [&](int least, int64_t bk) {   // until fewer than `least` are queued
+        __builtin_amdgcn_wave_barrier();
+        while (qc >= least) {
+            const int n = min(qc, 64);
+            qc -= n;
+            int p = 0;
+            if (lane == 0) p = atomicAdd(&bcnt[bk], n);
+            p = __builtin_amdgcn_readfirstlane(p) + lane;
+            if (lane < n && (uint32_t)p < (uint32_t)bcap) {
+                be[bk * bcap + p] = sQe[wv][qc + lane];
+                br[bk * bcap + p] = sQr[wv][qc + lane];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // a thread stages two 16-byte pieces of each operand; rows past the end
+    // repeat the last one (their distances are not offered)
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    u32x4 st[8];
+    const int pr = tid >> 2, po = (tid & 3) * 8;
+    auto load = [&](int64_t c0, int k0) {
+        const bool ok = k0 + po < dp;
+        const int k = ok ? k0 + po : 0;
+        const uint32_t keep = ok ? ~0u : 0u;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t qr = (row0 + min(q0 + pr + 64 * u, M - 1)) * dp + k, xr = min(c0 + pr + 64 * u, N - 1) * dp + k;
+            st[4 * u] = *reinterpret_cast<const u32x4 *>(Qh + qr) & keep;
+            st[4 * u + 1] = *reinterpret_cast<const u32x4 *>(Ql + qr) & keep;
+            st[4 * u + 2] = *reinterpret_cast<const u32x4 *>(Xh + xr) & keep;
+            st[4 * u + 3] = *reinterpret_cast<const u32x4 *>(Xl + xr) & keep;
+        }
+    };
+    load(cb, 0);
+    for (int64_t c0 = cb; c0 < ce; c0 += 128) {
+        f32x16 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+        for (int k0 = 0; k0 < dp; k0 += WF_K) {
+            __syncthreads();                // the previous pieces have been read
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int o = 0; o < 4; ++o)
+                    *reinterpret_cast<u32x4 *>(&sm[o][(pr + 64 * u) * WF_LD + po]) = st[4 * u + o];
+            __syncthreads();
+            if (k0 + WF_K < dp) load(c0, k0 + WF_K);
+            else if (c0 + 128 < ce) load(c0 + 128, 0);
+#pragma unroll
+            for (int s = 0; s < WF_K / 16; ++s) {
+                bf16x8 a[2][2], b[2][2];    // [block][high, low]
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        a[i][o] = ld_bf8(&sm[o][(64 * wr + 32 * i + l32) * WF_LD + 16 * s + 8 * half]);
+                        b[i][o] = ld_bf8(&sm[2 + o][(64 * wc + 32 * i + l32) * WF_LD + 16 * s + 8 * half]);
+                    }
+#pragma unroll
+                for (int o = 0; o < 3; ++o)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][o == 2], b[j][o == 1], acc[i][j],
+                                                                                0, 0, 0);
+            }
+        }
+        const uint32_t cw = (uint32_t)c0 + 64u * wc, cA = cw + (uint32_t)l32, cB = cA + 32u;
+        if (cw >= (uint32_t)ce) continue;   // (no barrier below)
+        const int64_t gA = min((int64_t)cA, N - 1), gB = min((int64_t)cB, N - 1);
+        const float ny0 = Xn[gA], ny1 = Xn[gB];
+        const uint32_t ce32 = (uint32_t)ce, m32 = (uint32_t)M;
+        const uint32_t qw = (uint32_t)q0 + 64u * wr;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            f32x16 dA = acc[i][0], dB = acc[i][1], th;
+            uint32_t regs = 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = 64 * wr + 32 * i + 8 * (r / 4) + 4 * half + (r % 4);
+                const float qn = sQn[row];
+                th[r] = sThr[row];
+                dA[r] = fmaf(-2.0f, dA[r], qn + ny0);
+                dB[r] = fmaf(-2.0f, dB[r], qn + ny1);
+                regs |= (__ballot(dA[r] <= th[r]) | __ballot(dB[r] <= th[r])) ? 1u << r : 0u;
+            }
+            acc[i][0] = dA;
+            acc[i][1] = dB;
+            while (regs) {
+                const int r = __builtin_ctz(regs);
+                regs &= regs - 1;
+                const float x = dA[r], y = dB[r], t = th[r];
+                const uint32_t qrow = qw + 32u * i + 4u * (uint32_t)half + (uint32_t)(8 * (r >> 2) + (r & 3));
+                const uint32_t self = excl ? qrow + (uint32_t)row0 : 0xffffffffu;
+                push(x <= t && cA < ce32 && cA != self, qrow, cA, x);
+                push(y <= t && cB < ce32 && cB != self, qrow, cB, y);
+                if (qc > FQ - 128) drain(64, qw >> 6);
+            }
+        }
+        drain(1, qw >> 6);
+        if (SYM && c0 > q0) {
+            // past the row block's own columns: offer each distance to the column too
+            const float tA = cA < ce32 ? Tin[gA] : -INFINITY, tB = cB < ce32 ? Tin[gB] : -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const f32x16 dA = acc[i][0], dB = acc[i][1];
+                uint32_t regs = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) regs |= (__ballot(dA[r] <= tA) | __ballot(dB[r] <= tB)) ? 1u << r : 0u;
+                while (regs) {
+                    const int r = __builtin_ctz(regs);
+                    regs &= regs - 1;
+                    const float x = dA[r], y = dB[r];
+                    const uint32_t qrow = qw + 32u * i + 4u * (uint32_t)half + (uint32_t)(8 * (r >> 2) + (r & 3));
+                    push(x <= tA && qrow < m32, cA, qrow, x);
+                    push(y <= tB && qrow < m32, cB, qrow, y);
+                    if (qc > FQ - 128) drain(64, cw >> 6);
+                }
+            }
+            drain(1, cw >> 6);
+        }
+    }
+}
+
 // A bucket's survivors by row: counts and first positions (in the bucket's part
 // of oe) of its 64 rows, in any order within a row.  A bucket that overflowed
 // marks all its rows (FILT_OVER).  One workgroup per bucket; each wave counts,
@@ -1186,6 +1376,21 @@ static void launch_filter(dim3 g, dim3 b, hipStream_t s, const uint16_t *Qh, con
     HIPC(hipGetLastError());
 }
 
+static void launch_filter_wide(dim3 g, hipStream_t s, const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int64_t M,
+                               const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int dp, int ex,
+                               int64_t row0, const float *T, const FilterBufs &B, bool sym, int win)
+{
+    if (sym) {
+        g.y = (unsigned)(((N + 127) / 128 + WF_PIECE - 1) / WF_PIECE);
+        hipLaunchKernelGGL(k_knn_filter_wide<true>, g, dim3(256), 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, dp, ex, row0, T,
+                           B.bcap, B.bcnt, B.be, B.br, 0);
+    } else {
+        hipLaunchKernelGGL(k_knn_filter_wide<false>, g, dim3(256), 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, dp, ex, row0, T,
+                           B.bcap, B.bcnt, B.be, B.br, win);
+    }
+    HIPC(hipGetLastError());
+}
+
 // Empty buckets before a sweep over m rows, and its survivors by row after it.
 static void filter_begin(const FilterBufs &B, int64_t m, hipStream_t s)
 {
@@ -1308,7 +1513,9 @@ static void filter_select(int dp, hipStream_t s, const uint16_t *Qh, const uint1
             HIPC(hipEventCreate(&ev->back()));
             HIPC(hipEventRecord((*ev)[ev->size() - 2], s));
         }
-        if (!tlist || nitems > 0)
+        if (dp > 128)
+            launch_filter_wide(g, s, Qh, Ql, Qn, m, Xh, Xl, Xn, N, dp, ex, r0, thr, B, sym, win);
+        else if (!tlist || nitems > 0)
             KNN_DISPATCH(launch_filter, g, dim3(256), s, Qh, Ql, Qn, m, Xh, Xl, Xn, N, ex, r0, thr, B, sym, win, tlist,
                          toff, items);
         if (ev) HIPC(hipEventRecord(ev->back(), s));
@@ -1729,6 +1936,12 @@ static bool build_tile_lists(const float *Xr, const float *thr_r, const float *X
     return true;
 }
 
+__global__ void k_unbound(const int32_t *__restrict__ rows, int n, float *__restrict__ thr)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) thr[rows[i]] = -3.0e38f;         // (an infinite one would certify)
+}
+
 void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int64_t M,
                     const uint16_t *Xh, const uint16_t *Xl, const float *Xn, int64_t N, int dp,
                     bool exclude_self, bool start_local, int32_t *cand, float *thr,
@@ -1745,7 +1958,10 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     dim3 grid((unsigned)((M + KB_M - 1) / KB_M)), block(256);
     int ex = exclude_self ? 1 : 0, sl = start_local ? 1 : 0;
     const int64_t ntiles = (N + KB_N - 1) / KB_N;
-    if (dp > 128) {
+    // more than 128 dimensions: the point set against itself is filtered as
+    // below; new points, which have no samples to bound them, sweep with lists
+    const bool wide = dp > 128;
+    if (wide && !(exclude_self && start_local && Qh == Xh && M == N)) {
         hipLaunchKernelGGL(k_knn_cand_wide, grid, block, 0, s, Qh, Ql, Qn, M, Xh, Xl, Xn, N, dp, ex, sl,
                            cand, thr);
         HIPC(hipGetLastError());
@@ -1770,7 +1986,8 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     const int64_t chunk = sym ? M : KNN_CHUNK;
     const int64_t mc = std::min<int64_t>(M, chunk);
     FilterBufs B;
-    B.nsel = std::max(1, std::min(nsel, KNN_CAND));
+    // (the certificate's margin grows with the dimension: all the candidates)
+    B.nsel = wide ? KNN_CAND : std::max(1, std::min(nsel, KNN_CAND));
     int32_t *retry, *over;
     std::vector<void *> ttmp;
     auto ta = [&](size_t b) {
@@ -1830,7 +2047,13 @@ void knn_candidates(const uint16_t *Qh, const uint16_t *Ql, const float *Qn, int
     // 64th distance)
     const int32_t *list = retry + 1;
     int32_t nlist = nretry;
-    if (nretry > 0 && nretry <= mc && exclude_self && Qh == Xh) {
+    if (wide && nretry > 0) {
+        // no certificate: these rows take the fallback at the bound of their
+        // stored candidates
+        hipLaunchKernelGGL(k_unbound, dim3((unsigned)((nretry + 255) / 256)), dim3(256), 0, s, list, nretry, thr);
+        HIPC(hipGetLastError());
+        nlist = 0;
+    } else if (nretry > 0 && nretry <= mc && exclude_self && Qh == Xh) {
         // the point set against itself: the sampled thresholds (large sets) on
         // compact copies of the rows, then the filter over all points (one
         // pass: the rows fit the filter buffers)
@@ -2151,93 +2374,6 @@ void knn_exact_rows(const float *Q, const float *X, int64_t N, int d, int dp, in
 }
 
 // ---------------------------------------------------------------- filtered fallback
-// Threshold sweep for rows wider than 128 dimensions (dimension chunks of
-// 128 through LDS, as k_knn_cand_wide): every point whose approximate
-// distance to row i is at most T_i is appended to the row's segment.
-__global__ __launch_bounds__(256) void k_knn_filter_wide(const uint16_t *__restrict__ Qh,
-                                                         const uint16_t *__restrict__ Ql,
-                                                         const float *__restrict__ Qn, int64_t M,
-                                                         const uint16_t *__restrict__ Xh,
-                                                         const uint16_t *__restrict__ Xl,
-                                                         const float *__restrict__ Xn, int64_t N, int dp,
-                                                         const float *__restrict__ Tin, int cap,
-                                                         int32_t *__restrict__ ocnt, uint2 *__restrict__ oe)
-{
-    constexpr int KC = 128;
-    constexpr int LDB = KC + 8;
-    __shared__ __attribute__((aligned(16))) uint16_t sBh[KB_N * LDB];
-    __shared__ __attribute__((aligned(16))) uint16_t sBl[KB_N * LDB];
-    __shared__ float sBn[KB_N];
-    const int tid = threadIdx.x, lane = tid % WAVE;
-    const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
-    const int half = lane >> 5, l32 = lane & 31;
-    const int64_t q0 = (int64_t)blockIdx.x * KB_M + wv * 32;
-    const int64_t arow = q0 + l32;
-    const bool aok = arow < M;
-    float qn[16], thrv[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        int64_t row = q0 + 8 * (r / 4) + 4 * half + (r % 4);
-        qn[r] = row < M ? Qn[row] : 0.0f;
-        thrv[r] = row < M ? Tin[row] : -INFINITY;
-    }
-    const int64_t ntiles = (N + KB_N - 1) / KB_N;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int64_t tbase = t * KB_N;
-        f32x16 acc0 = {}, acc1 = {};
-        for (int k0 = 0; k0 < dp; k0 += KC) {
-            const int kc = min(KC, dp - k0);
-            __syncthreads();
-            for (int c = tid; c < KB_N * (KC / 8); c += 256) {
-                int row = c / (KC / 8), off = (c % (KC / 8)) * 8;
-                int64_t g = tbase + row;
-                uint4 vh = {0, 0, 0, 0}, vl = {0, 0, 0, 0};
-                if (g < N && off < kc) {
-                    vh = *reinterpret_cast<const uint4 *>(Xh + g * dp + k0 + off);
-                    vl = *reinterpret_cast<const uint4 *>(Xl + g * dp + k0 + off);
-                }
-                *reinterpret_cast<uint4 *>(&sBh[row * LDB + off]) = vh;
-                *reinterpret_cast<uint4 *>(&sBl[row * LDB + off]) = vl;
-            }
-            if (k0 == 0 && tid < KB_N) {
-                int64_t g = tbase + tid;
-                sBn[tid] = g < N ? Xn[g] : 0.0f;
-            }
-            __syncthreads();
-            for (int s = 0; s < kc / 16; ++s) {
-                bf16x8 qa = aok ? ld_bf8(Qh + arow * dp + k0 + 16 * s + 8 * half) : bf16x8{};
-                bf16x8 qb = aok ? ld_bf8(Ql + arow * dp + k0 + 16 * s + 8 * half) : bf16x8{};
-                bf16x8 bh0 = ld_bf8(&sBh[l32 * LDB + 16 * s + 8 * half]);
-                bf16x8 bl0 = ld_bf8(&sBl[l32 * LDB + 16 * s + 8 * half]);
-                bf16x8 bh1 = ld_bf8(&sBh[(32 + l32) * LDB + 16 * s + 8 * half]);
-                bf16x8 bl1 = ld_bf8(&sBl[(32 + l32) * LDB + 16 * s + 8 * half]);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, bh0, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, bh1, acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, bl0, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, bl1, acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qb, bh0, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qb, bh1, acc1, 0, 0, 0);
-            }
-        }
-        const float ny0 = sBn[l32], ny1 = sBn[32 + l32];
-        const int64_t cA = tbase + l32, cB = cA + 32;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t qrow = q0 + 8 * (r / 4) + 4 * half + (r % 4);
-            const float dA = fmaf(-2.0f, acc0[r], qn[r] + ny0);
-            const float dB = fmaf(-2.0f, acc1[r], qn[r] + ny1);
-            if (dA <= thrv[r] && cA < N) {
-                int p = atomicAdd(&ocnt[qrow], 1);
-                if (p < cap) oe[qrow * cap + p] = make_uint2(__float_as_uint(dA), (uint32_t)cA);
-            }
-            if (dB <= thrv[r] && cB < N) {
-                int p = atomicAdd(&ocnt[qrow], 1);
-                if (p < cap) oe[qrow * cap + p] = make_uint2(__float_as_uint(dB), (uint32_t)cB);
-            }
-        }
-    }
-}
-
 __global__ void k_gather_qrows(const int32_t *__restrict__ rows, int64_t n, int dp,
                                const uint16_t *__restrict__ Qh, const uint16_t *__restrict__ Ql,
                                const float *__restrict__ Qn, const float *__restrict__ tb,
@@ -2281,8 +2417,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const int32_t *__restrict__ 
         if (lane == 0) over_rows[atomicAdd(over_count, 1)] = (int32_t)row;
         return;
     }
-    // by row within the bucket's part, or cap entries per row (rstart NULL)
-    const uint2 *re = rstart ? oe + (i >> 6) * bcap + rstart[i] : oe + i * cap;
+    const uint2 *re = oe + (i >> 6) * bcap + rstart[i];
     double bD = INFINITY;
     int bj = 0x7fffffff;
     for (int c0 = 0; c0 < cnt; c0 += 64) {
@@ -2346,30 +2481,21 @@ void knn_fallback(const float *Q, const uint16_t *Qh, const uint16_t *Ql, const 
     uint16_t *Bh = (uint16_t *)ta(sizeof(uint16_t) * n * dp), *Bl = (uint16_t *)ta(sizeof(uint16_t) * n * dp);
     float *Bn = (float *)ta(sizeof(float) * n), *Bt = (float *)ta(sizeof(float) * n);
     FilterBufs B;
-    if (dp > 128) {
-        B.cap = FCAP;
-        B.ocnt = (int32_t *)ta(sizeof(int32_t) * n);
-        B.oe = (uint2 *)ta(sizeof(uint2) * n * FCAP);
-    } else {
-        B.alloc(n, FCAP, FCAP, ta);
-    }
+    B.alloc(n, FCAP, FCAP, ta);
     int32_t *over = (int32_t *)ta(sizeof(int32_t) * (n + 1));
     hipLaunchKernelGGL(k_gather_qrows, dim3((unsigned)n), dim3(128), 0, s, rows, n, dp, Qh, Ql, Qn, tbound, Bh, Bl,
                        Bn, Bt);
     HIPC(hipMemsetAsync(over, 0, sizeof(int32_t), s));
     dim3 g((unsigned)((n + KB_M - 1) / KB_M)), block(256);
-    if (dp > 128) {
-        HIPC(hipMemsetAsync(B.ocnt, 0, sizeof(int32_t) * n, s));
-        hipLaunchKernelGGL(k_knn_filter_wide, g, block, 0, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, dp, Bt, FCAP, B.ocnt,
-                           B.oe);
-    } else {
-        // few rows: the points are split into column segments, one workgroup
-        // each, appending to the rows' common outputs
-        g.y = (unsigned)filter_segments(n, (N + KB_N - 1) / KB_N);
-        filter_begin(B, n, s);
+    // few rows: the points are split into column segments, one workgroup each,
+    // appending to the rows' common outputs
+    g.y = (unsigned)filter_segments(n, (N + KB_N - 1) / KB_N);
+    filter_begin(B, n, s);
+    if (dp > 128)
+        launch_filter_wide(g, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, dp, 0, 0, Bt, B, false, 0);
+    else
         KNN_DISPATCH(launch_filter, g, block, s, Bh, Bl, Bn, n, Xh, Xl, Xn, N, 0, 0, Bt, B, false);
-        filter_rows(B, n, s);
-    }
+    filter_rows(B, n, s);
     HIPC(hipGetLastError());
     hipLaunchKernelGGL(k_knn_rerank, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, rows, (int64_t)0, n, Q, X, d,
                        dp, kappa, exclude_self ? 1 : 0, FCAP, B.ocnt, B.rstart, B.bcap, B.oe, idmap, rowmap, idx, dist,

@@ -44,3 +44,17 @@ def test_lists_bit_exact(N, d, kappa, m, dup):
             keep[-1] = False
         assert np.array_equal(gi[r], oi[a][keep]), f"row {r}"
         assert np.array_equal(gd[r], od[a][keep]), f"row {r}"
+
+
+WIDE = [  # N, d, kappa, leaf, coincident points
+    (200, 129, 16, 64, 0), (129, 300, 64, 64, 0), (4097, 144, 32, 256, 0), (5000, 150, 8, 128, 1500), (3000, 1000, 49, 512, 0),
+    (33001, 200, 16, 512, 0), (34000, 136, 32, 512, 2000),
+]
+
+
+@pytest.mark.parametrize("N,d,kappa,m,dup", WIDE)
+def test_wide_lists_bit_exact(N, d, kappa, m, dup):
+    """More than 128 dimensions: column segments, windows and the triangular
+    sweep, partial blocks of rows, columns and dimensions, rows without a
+    certificate."""
+    test_lists_bit_exact(N, d, kappa, m, dup)
