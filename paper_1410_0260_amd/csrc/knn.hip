@@ -715,14 +715,18 @@ __global__ __launch_bounds__(256, KS <= 4 ? 3 : 2) void k_knn_filter(const uint1
         }
         qc += __popcll(m);
     };
+    bool full = false;                      // the wave's bucket has overflowed: its count stays bounded
     auto drain = [&](int least) {           // until fewer than `least` are queued
         __builtin_amdgcn_wave_barrier();
         while (qc >= least) {
             const int n = min(qc, 64);
             qc -= n;
+            if (full) continue;
             int p = 0;
             if (lane == 0) p = atomicAdd(&bcnt[bk0], n);
-            p = __builtin_amdgcn_readfirstlane(p) + lane;
+            p = __builtin_amdgcn_readfirstlane(p);
+            full = p >= bcap;
+            p += lane;
             if (lane < n && (uint32_t)p < (uint32_t)bcap) {
                 be[bk0 * bcap + p] = sQe[wv][qc + lane];
                 br[bk0 * bcap + p] = sQr[wv][qc + lane];
